@@ -13,7 +13,7 @@
 //                 and hands the two ends reached to the next lane; an
 //                 interval that has shrunk to one value is the true start.
 //                 Runs that meet a clamp from both ends settle the next lane
-//                 at once, and after at most 63 rounds every start is known
+//                 at once, and after one round per run every start is known
 //                 (the sequential order, in the worst case).
 //                 Variants: the entropies may be the GQA group's means
 //                 (binary64 sum in head order / G, rounded to binary32), and
@@ -38,8 +38,17 @@ namespace ei {
 namespace {
 
 constexpr int kThreads = 256;
+// The budget recurrence takes chunks of kWave runs of kRun steps, a run per
+// lane.  A run is kRun steps long for any number of segments (a short layer
+// uses fewer lanes): the worst case, a budget off both clamps, is then one
+// round per run, where runs shortened to fill the wave took one per lane
+// (8 segments: 63 rounds and 13.8 us; now no round, 10.9 us less).
 constexpr int kChunk = 1024;
-constexpr int kRunMax = kChunk / kWave;   // steps per lane in the budget recurrence
+constexpr int kRun = kChunk / kWave;
+// Step i of a chunk (step j = i % kRun of lane l = i / kRun) sits at
+// j * kRunStride + l: a lane-wise read of step j and the increments' writes of
+// consecutive steps both spread over the LDS banks.
+constexpr int kRunStride = kWave + 1;
 
 // Lane l receives lane l - 1's v (lane 0 keeps its own): a DPP wave shift.
 __device__ __forceinline__ double shift_up1(double v) {
@@ -54,8 +63,8 @@ __global__ __launch_bounds__(kThreads) void budget_kernel(
     const float* __restrict__ entropy, int Hq, int CS, int r, int Lb, float e_t, double alpha,
     double delta_t, int Bh, int mult, int mode, int G, uint8_t* __restrict__ rigid_out,
     int32_t* __restrict__ k_out) {
-  __shared__ double delta[kChunk];   // -inf: the segment restarts at B_h
-  __shared__ double Bs[kChunk];
+  __shared__ double delta[kRun * kRunStride];   // -inf: the segment restarts at B_h
+  __shared__ double Bs[kRun * kRunStride];
   const int64_t bh = blockIdx.x;
   int32_t* ko = k_out + bh * CS;
   const int tid = threadIdx.x;
@@ -74,22 +83,16 @@ __global__ __launch_bounds__(kThreads) void budget_kernel(
   const double B0 = (double)Bh;
   const double cap = (double)mult * B0;
   const double a = alpha * B0;
-  // The increments of the chunk of steps at c0 (n steps) into delta.  The
-  // steps are padded with zero increments to a whole number of waves (a zero
-  // increment leaves a clamped value unchanged) and split into kWave runs of
-  // L consecutive steps; step i = l L + j of lane l's run is held at
-  // delta[j kWave + l], so every lane's reads and writes of a step are one
-  // conflict-free row.  Up to four steps per thread, with selects rather
-  // than branches so that their loads issue together (a padding step reads
-  // an unused segment).  Returns 0 if a segment of the chunk is not below
-  // e_t.
+  // The increments of the chunk of steps at c0 (n steps) into delta, padded
+  // with zero increments to whole runs (a zero increment leaves a clamped
+  // value unchanged).  Up to four steps per thread, with selects rather than
+  // branches so that their loads issue together (a padding step reads an
+  // unused segment).  Returns 0 if a segment of the chunk is not below e_t.
   auto increments = [&](int c0, int n) {
-    const int npad = (n + kWave - 1) / kWave * kWave;
-    const int L = npad / kWave;
+    const int npad = (n + kRun - 1) / kRun * kRun;
     int low = 1;
 #pragma unroll 4
-    for (int p = tid; p < npad; p += kThreads) {
-      const int i = (p % kWave) * L + p / kWave;
+    for (int i = tid; i < npad; i += kThreads) {
       const int s = c0 + min(i, n - 1);
       const float es = E(s), eprev = E(max(s - 1, 0));
       if (!(es < e_t)) low = 0;
@@ -100,7 +103,7 @@ __global__ __launch_bounds__(kThreads) void budget_kernel(
       // B_0 = B_h, and a rigid segment of the per-segment rule takes B_h:
       // B_prev + (-inf) is clamped to exactly B_h below
       d = (s == 0 || (mode == EI_CLASSIFY_SEGMENT && es < e_t)) ? -INFINITY : d;
-      delta[p] = i < n ? d : 0.0;
+      delta[(i % kRun) * kRunStride + i / kRun] = i < n ? d : 0.0;
     }
     return low;
   };
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(kThreads) void budget_kernel(
   double Bprev = B0;   // wave 0: B before the chunk's first step
   for (int c0 = 0; c0 < CS; c0 += kChunk) {
     const int n = min(kChunk, CS - c0);
-    const int L = (n + kWave - 1) / kWave, npad = L * kWave;
+    const int runs = (n + kRun - 1) / kRun;
     if (c0 > 0) increments(c0, n);   // the first chunk's are in delta already
     __syncthreads();
     if (tid < kWave) {
@@ -131,9 +134,9 @@ __global__ __launch_bounds__(kThreads) void budget_kernel(
       auto step = [&](double x, double d) { return fmin(fmax(x + d, B0), cap); };
       const double lo = step(B0, -INFINITY), hi = step(B0, INFINITY);
       const int lane = tid;
-      double dv[kRunMax];   // the lane's increments (entries j >= L unused)
+      double dv[kRun];   // the lane's increments (unset in lanes past the runs)
 #pragma unroll
-      for (int j = 0; j < kRunMax; ++j) dv[j] = delta[j * kWave + lane];
+      for (int j = 0; j < kRun; ++j) dv[j] = delta[j * kRunStride + lane];
       // A step is monotone in x, so a run evaluated from the two ends of an
       // interval holding its true start bounds every true value of the run.
       // Each round every lane runs its steps from both ends of its start
@@ -141,20 +144,23 @@ __global__ __launch_bounds__(kThreads) void budget_kernel(
       // start interval.  Lane 0 starts from the carried B itself; a lane whose
       // start interval is one value (equal bit patterns) has its true start,
       // and so does its successor one round later at the latest, so after at
-      // most kWave - 1 rounds every start is known.  Runs that meet a clamp
+      // most runs - 1 rounds every run's start is known (lanes past the runs
+      // count as settled; nothing flows from them).  Runs that meet a clamp
       // from both ends settle their successors much sooner.  (The one thing
       // the bounds cannot settle is the sign of a zero budget, which no k_s
       // depends on.)
+      const uint64_t idle = runs < kWave ? ~0ull << runs : 0ull;
       double pl = lane == 0 ? Bprev : lo, ph = lane == 0 ? Bprev : hi;
-      while (__builtin_amdgcn_ballot_w64(__double_as_longlong(pl) ==
-                                         __double_as_longlong(ph)) != ~0ull) {
+      for (int round = 1; round < runs; ++round) {
+        if ((__builtin_amdgcn_ballot_w64(__double_as_longlong(pl) ==
+                                         __double_as_longlong(ph)) | idle) == ~0ull)
+          break;
         double xl = pl, xh = ph;
 #pragma unroll
-        for (int j = 0; j < kRunMax; ++j)
-          if (j < L) {
-            xl = step(xl, dv[j]);
-            xh = step(xh, dv[j]);
-          }
+        for (int j = 0; j < kRun; ++j) {
+          xl = step(xl, dv[j]);
+          xh = step(xh, dv[j]);
+        }
         xl = shift_up1(xl);
         xh = shift_up1(xh);
         if (lane > 0) {
@@ -165,19 +171,16 @@ __global__ __launch_bounds__(kThreads) void budget_kernel(
       // every lane from its true start, in the recurrence's own order
       double x = pl;
 #pragma unroll
-      for (int j = 0; j < kRunMax; ++j)
-        if (j < L) {
-          x = step(x, dv[j]);
-          Bs[j * kWave + lane] = x;
-        }
-      Bprev = __shfl(x, kWave - 1);
+      for (int j = 0; j < kRun; ++j) {
+        x = step(x, dv[j]);
+        Bs[j * kRunStride + lane] = x;
+      }
+      Bprev = __shfl(x, kWave - 1);   // used after a whole chunk only
     }
     __syncthreads();
-    for (int p = tid; p < npad; p += kThreads) {
-      const int i = (p % kWave) * L + p / kWave;
-      if (i >= n) continue;
+    for (int i = tid; i < n; i += kThreads) {
       const int s = c0 + i;
-      const int64_t kb = (int64_t)floor(Bs[p] / (double)Lb);
+      const int64_t kb = (int64_t)floor(Bs[(i % kRun) * kRunStride + i / kRun] / (double)Lb);
       ko[s] = (int32_t)min(kb, (int64_t)s * r);
     }
     __syncthreads();

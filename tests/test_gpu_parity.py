@@ -569,6 +569,36 @@ def test_budget_recurrence_off_the_clamps(mode):
         np.testing.assert_array_equal(g[name], ref[name], err_msg=f"{name} mode={mode}")
 
 
+@pytest.mark.parametrize("CS", [1, 2, 15, 16, 17, 63, 64, 65, 1023, 1024, 1025, 1040])
+def test_budget_run_edges(CS):
+    """Segment counts around the edges of the budget kernel's 16-step runs and
+    1024-step chunks, with budgets off both clamps (every run has to wait for
+    the one before it), under each classification rule: bit-exact against the
+    oracle."""
+    Ls, Lb, Hq = 128, 64, 4
+    N, CB = CS * Ls, 2 * CS
+    rng = np.random.default_rng(CS)
+    en = np.empty((1, Hq, CS), np.float64)
+    for h in range(Hq):
+        e = [1.0]
+        for s in range(1, CS):
+            u = 2.4 if s == 1 else rng.uniform(0.395, 0.405) if h % 2 == 0 else rng.uniform(0.2, 0.6)
+            e.append(e[-1] * (1.0 - u if u < 1.0 and e[-1] > 1.0 else 1.0 + u))
+        en[0, h] = e
+    en = en.astype(np.float32)
+    if CS > 20:
+        en[0, 3, CS // 2:] = 1e-7                 # below e_t: the per-segment rule restarts
+    ls = rng.standard_normal((1, Hq, CS, CB)).astype(np.float32)
+    for mode in (eb.CLASSIFY_HEAD, eb.CLASSIFY_GQA_GROUP, eb.CLASSIFY_SEGMENT):
+        sel = eb.select_blocks(torch.from_numpy(ls).cuda(), torch.from_numpy(en).cuda(), N, Ls, Lb,
+                               1e-5, 0.5, 0.4, 2048, 3, n_kv_heads=2, mode=mode)
+        torch.cuda.synchronize()
+        ref = oracle.select(ls, en, N, Ls, Lb, 1e-5, 0.5, 0.4, 2048, 3, mode=mode, n_kv_heads=2)
+        for name in ("rigid", "budget", "cnt", "idx"):
+            np.testing.assert_array_equal(sel[name].cpu().numpy(), ref[name],
+                                          err_msg=f"{name} CS={CS} mode={mode}")
+
+
 @pytest.mark.parametrize("mode", [eb.CLASSIFY_HEAD, eb.CLASSIFY_GQA_GROUP, eb.CLASSIFY_SEGMENT])
 @pytest.mark.parametrize("e_t", [1e-5, math.inf])
 def test_select_modes_match_oracle(mode, e_t):
