@@ -370,6 +370,38 @@ ei_status ei_entropy_guided_prefill_noalloc(const uint16_t* q, const uint16_t* k
                                             int32_t* block_idx, int32_t* block_cnt, uint16_t* o,
                                             void* stream);
 
+/*
+ * The passes of a decoder layer between its matrix products (RMSNorm with the
+ * residual sum before it, rotary embedding with the change to head-major
+ * layout, SwiGLU), each one pass over memory.  They carry no part of the
+ * method; prefill.py runs them around the attention.  bf16 tensors,
+ * contiguous, fp32 arithmetic.  Pointers and alignment as above (the fp32
+ * tables also start on a 16-byte boundary).
+ *
+ * ei_add_rmsnorm: s = x + y rounded to bf16 (s = x when y is NULL), written to
+ * sum_out (ignored when y is NULL; may be x or y itself), and
+ * out = s / sqrt(mean(s^2) + eps) * gain over each of the rows.  cols must be
+ * a multiple of 8 up to 16384 (else EI_ERR_UNSUPPORTED).
+ */
+ei_status ei_add_rmsnorm(const uint16_t* x, const uint16_t* y, const uint16_t* gain, int64_t rows,
+                         int32_t cols, float eps, uint16_t* sum_out, uint16_t* out, void* stream);
+
+/*
+ * ei_rope_heads: q_in [B][N][Hq][D], k_in and v_in [B][N][Hkv][D] to q_out
+ * [B][Hq][N][D], k_out and v_out [B][Hkv][N][D], with the pairs
+ * (i, i + D/2) of q and k rotated by the angle whose cosine and sine are
+ * cos_table[n][i] and sin_table[n][i] (fp32 [N][D/2]).  D must be 128.
+ */
+ei_status ei_rope_heads(const uint16_t* q_in, const uint16_t* k_in, const uint16_t* v_in,
+                        const float* cos_table, const float* sin_table, ei_dims dims,
+                        uint16_t* q_out, uint16_t* k_out, uint16_t* v_out, void* stream);
+
+/*
+ * ei_swiglu: out[i] = bf16(silu(g[i])) * u[i] for n elements (a multiple of 8,
+ * else EI_ERR_UNSUPPORTED); out may be g or u.
+ */
+ei_status ei_swiglu(const uint16_t* g, const uint16_t* u, int64_t n, uint16_t* out, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -104,6 +104,13 @@ def lib() -> ctypes.CDLL:
         L.ei_dense_prefill_attn.restype = ctypes.c_int
         L.ei_dense_prefill_attn.argtypes = [_VP, _VP, _VP, Dims, ctypes.c_float, ctypes.c_int32,
                                             _VP, _VP]
+        L.ei_add_rmsnorm.restype = ctypes.c_int
+        L.ei_add_rmsnorm.argtypes = [_VP, _VP, _VP, ctypes.c_int64, ctypes.c_int32, ctypes.c_float,
+                                     _VP, _VP, _VP]
+        L.ei_rope_heads.restype = ctypes.c_int
+        L.ei_rope_heads.argtypes = [_VP, _VP, _VP, _VP, _VP, Dims, _VP, _VP, _VP, _VP]
+        L.ei_swiglu.restype = ctypes.c_int
+        L.ei_swiglu.argtypes = [_VP, _VP, ctypes.c_int64, _VP, _VP]
         _LIB = L
     return _LIB
 
@@ -429,3 +436,62 @@ def entropy_guided_prefill(q, k, v, seg_len: int = 128, block_len: int = 64,
     _check(fn, st)
     sel = {n: bufs[n] for n in ("rigid", "budget", "idx", "cnt")}
     return bufs["out"], sel, bufs["log_scores"], bufs["entropy"]
+
+
+def add_rmsnorm(x, y, gain, eps: float):
+    """ei_add_rmsnorm over the last dimension of x (bf16, contiguous): returns
+    (x + y, its RMSNorm times gain), or (x, norm of x) when y is None."""
+    _req(x, "x", torch.bfloat16, x.dim())
+    _req(gain, "gain", torch.bfloat16, 1)
+    cols = x.shape[-1]
+    if gain.numel() != cols:
+        raise ValueError(f"gain has {gain.numel()} elements for {cols} columns")
+    if y is not None:
+        _req(y, "y", torch.bfloat16, x.dim())
+        if y.shape != x.shape:
+            raise ValueError(f"y {tuple(y.shape)} does not match x {tuple(x.shape)}")
+    _same_device(x, gain, y)
+    s = x if y is None else torch.empty_like(x)
+    out = torch.empty_like(x)
+    with torch.cuda.device(x.device):
+        st = lib().ei_add_rmsnorm(_ptr(x), _ptr(y), _ptr(gain), x.numel() // cols, cols, float(eps),
+                                  _ptr(s), _ptr(out), _stream(x))
+    _check("ei_add_rmsnorm", st)
+    return s, out
+
+
+def rope_heads(q, k, v, cos, sin):
+    """ei_rope_heads: q [B, N, Hq, D], k and v [B, N, Hkv, D] (bf16) to
+    head-major [B, H, N, D], q and k rotated by the tables cos / sin [N, D/2]."""
+    for t, n in ((q, "q"), (k, "k"), (v, "v")):
+        _req(t, n, torch.bfloat16, 4)
+    B, N, Hq, D = q.shape
+    Hkv = k.shape[2]
+    if tuple(k.shape) != (B, N, Hkv, D) or v.shape != k.shape or Hkv <= 0 or Hq % Hkv:
+        raise ValueError(f"k {tuple(k.shape)} / v {tuple(v.shape)} do not match q {tuple(q.shape)}")
+    for t, n in ((cos, "cos"), (sin, "sin")):
+        _req(t, n, torch.float32, 2)
+        if tuple(t.shape) != (N, D // 2):
+            raise ValueError(f"{n} {tuple(t.shape)} is not [{N}, {D // 2}]")
+    _same_device(q, k, v, cos, sin)
+    out = [torch.empty((B, t.shape[2], N, D), dtype=t.dtype, device=t.device) for t in (q, k, v)]
+    with torch.cuda.device(q.device):
+        st = lib().ei_rope_heads(_ptr(q), _ptr(k), _ptr(v), _ptr(cos), _ptr(sin),
+                                 Dims(B, Hq, Hkv, N, D), *(_ptr(t) for t in out), _stream(q))
+    _check("ei_rope_heads", st)
+    return out
+
+
+def swiglu(g, u, out=None):
+    """ei_swiglu: silu(g) * u (bf16, contiguous); ``out`` may be g or u."""
+    _req(g, "g", torch.bfloat16, g.dim())
+    _req(u, "u", torch.bfloat16, g.dim())
+    out = torch.empty_like(g) if out is None else out
+    _req(out, "out", torch.bfloat16, g.dim())
+    if u.shape != g.shape or out.shape != g.shape:
+        raise ValueError("g / u / out shapes differ")
+    _same_device(g, u, out)
+    with torch.cuda.device(g.device):
+        st = lib().ei_swiglu(_ptr(g), _ptr(u), g.numel(), _ptr(out), _stream(g))
+    _check("ei_swiglu", st)
+    return out

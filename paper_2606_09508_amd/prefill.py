@@ -6,11 +6,12 @@ entropy probe, head classification / budgets / top-k selection and the
 block-sparse kernel, in the library's one call (``attn="sparse"``), or the
 dense causal kernel
 (``attn="dense"``, the full-attention baseline).  Everything around the
-attention is the ordinary decoder layer -- RMSNorm, the Q/K/V/O projections,
-rotary position embedding, the SwiGLU MLP -- on PyTorch (the projections and
-MLP are plain library GEMMs); it is the harness that gives time-to-first-token
-(TTFT) against prompt length, the end-to-end setting of Section 5's latency
-study, and carries no part of the method.
+attention is the ordinary decoder layer: the Q/K/V/O projections and the MLP
+are plain library GEMMs, and RMSNorm, the rotary position embedding and SwiGLU
+are one pass each in this library's kernels (or plain PyTorch, for inputs they
+do not take).  It is the harness that gives time-to-first-token (TTFT) against
+prompt length, the end-to-end setting of Section 5's latency study, and
+carries no part of the method.
 
     python -m paper_2606_09508_amd.prefill --ttft      # markdown table on stdout
 """
@@ -124,23 +125,83 @@ class Attention:
         return o
 
 
-def layer_forward(x, w, shape: DecoderShape, attn: Attention, cos, sin, trace=None):
-    """One decoder layer on x [B, N, hidden] bf16; returns the new hidden
-    state.  trace (optional dict) receives the attention inputs and output."""
+def _plain(*ts) -> bool:
+    """Whether a kernel call on these tensors computes all that the tensor
+    operations would: ordinary tensors of one GPU, and nothing that the call
+    would be invisible to (autograd, forward-mode and functorch transforms,
+    tensor subclasses, a compiler's tracing)."""
+    dev = ts[0].device
+    return (dev.type == "cuda"
+            and all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.device == dev for t in ts)
+            and not torch.compiler.is_compiling()
+            and torch._C._functorch.peek_interpreter_stack() is None
+            and torch.autograd.forward_ad._current_level < 0
+            and not (torch.is_grad_enabled() and any(t.requires_grad for t in ts)))
+
+
+def _dense16(*ts) -> bool:
+    return all(t.is_contiguous() and t.data_ptr() % 16 == 0 for t in ts)
+
+
+def _norm_fits(x, gain) -> bool:
+    """Sizes, types and layout ei_add_rmsnorm takes."""
+    H = x.shape[-1]
+    return (x.numel() > 0 and H % 8 == 0 and H <= 16384 and tuple(gain.shape) == (H,)
+            and x.dtype == gain.dtype == torch.bfloat16 and _dense16(x, gain))
+
+
+def _one_pass(x, w, shape: DecoderShape, cos, sin) -> bool:
+    """Whether the layer's norms, rotary embedding and SwiGLU run in this
+    library's one-pass kernels; what those do not take goes through the tensor
+    operations, which accept any of it."""
+    return (_plain(x, cos, sin, *w.values()) and shape.head_dim == 128
+            and shape.n_q_heads % shape.n_kv_heads == 0
+            and w["w_gate"].shape == w["w_up"].shape and w["w_gate"].shape[-1] % 8 == 0
+            and all(t.dtype == torch.bfloat16 for t in w.values())
+            and _norm_fits(x, w["norm1"]) and _norm_fits(x, w["norm2"])
+            and all(t.dtype == torch.float32 and tuple(t.shape) == (x.shape[1], 64)
+                    for t in (cos, sin)) and _dense16(cos, sin))
+
+
+def _layer(x, y, w, shape: DecoderShape, attn: Attention, cos, sin, trace=None):
+    """One decoder layer on the hidden state x + y (y None: x itself); returns
+    the new hidden state as two summands, so that a following layer's norm
+    takes their sum in the pass that reads it."""
     B, N, _ = x.shape
     Hq, Hkv, D = shape.n_q_heads, shape.n_kv_heads, shape.head_dim
-    h = _rmsnorm(x, w["norm1"], shape.rms_eps)
-    q = (h @ w["wq"]).view(B, N, Hq, D).transpose(1, 2).contiguous()
-    k = (h @ w["wk"]).view(B, N, Hkv, D).transpose(1, 2).contiguous()
-    v = (h @ w["wv"]).view(B, N, Hkv, D).transpose(1, 2).contiguous()
-    q, k = _rope(q, cos, sin), _rope(k, cos, sin)
+    one_pass = _one_pass(x, w, shape, cos, sin)
+    if one_pass:
+        x, h = eb.add_rmsnorm(x, y, w["norm1"], shape.rms_eps)
+    else:
+        x = x if y is None else x + y
+        h = _rmsnorm(x, w["norm1"], shape.rms_eps)
+    q, k, v = ((h @ w[n]).view(B, N, heads, D)
+               for n, heads in (("wq", Hq), ("wk", Hkv), ("wv", Hkv)))
+    if one_pass:
+        q, k, v = eb.rope_heads(q, k, v, cos, sin)
+    else:
+        q, k, v = (t.transpose(1, 2).contiguous() for t in (q, k, v))
+        q, k = _rope(q, cos, sin), _rope(k, cos, sin)
     o = attn(q, k, v)
     if trace is not None:
         trace.update(q=q.clone(), k=k.clone(), v=v.clone(), o=o.clone())
-    x = x + o.transpose(1, 2).reshape(B, N, Hq * D) @ w["wo"]
-    h = _rmsnorm(x, w["norm2"], shape.rms_eps)
-    x = x + (torch.nn.functional.silu(h @ w["w_gate"]) * (h @ w["w_up"])) @ w["w_down"]
-    return x
+    y = o.transpose(1, 2).reshape(B, N, Hq * D) @ w["wo"]
+    if one_pass and _plain(x, y):   # (the attention may be a caller's own, with gradients)
+        x, h = eb.add_rmsnorm(x, y, w["norm2"], shape.rms_eps)
+        g = h @ w["w_gate"]
+        m = eb.swiglu(g, h @ w["w_up"], out=g)
+    else:
+        x = x + y
+        h = _rmsnorm(x, w["norm2"], shape.rms_eps)
+        m = torch.nn.functional.silu(h @ w["w_gate"]) * (h @ w["w_up"])
+    return x, m @ w["w_down"]
+
+
+def layer_forward(x, w, shape: DecoderShape, attn: Attention, cos, sin, trace=None):
+    """One decoder layer on x [B, N, hidden] bf16; returns the new hidden
+    state.  trace (optional dict) receives the attention inputs and output."""
+    x, y = _layer(x, None, w, shape, attn, cos, sin, trace)
+    return x + y
 
 
 def prefill(x, layers, shape: DecoderShape, attn: Attention, lm_head=None):
@@ -149,9 +210,15 @@ def prefill(x, layers, shape: DecoderShape, attn: Attention, lm_head=None):
     head [hidden, vocab] is given) -- what the first generated token needs."""
     N = x.shape[1]
     cos, sin = rope_tables(N, shape.head_dim, shape.rope_theta, x.device)
+    y = None
     for w in layers:
-        x = layer_forward(x, w, shape, attn, cos, sin)
-    last = _rmsnorm(x[:, -1:], layers[-1]["norm2"], shape.rms_eps)
+        x, y = _layer(x, y, w, shape, attn, cos, sin)
+    last = x[:, -1:] if y is None else x[:, -1:] + y[:, -1:]
+    gain = layers[-1]["norm2"]
+    if _plain(last, gain) and _norm_fits(last, gain):
+        last = eb.add_rmsnorm(last, None, gain, shape.rms_eps)[1]
+    else:
+        last = _rmsnorm(last, gain, shape.rms_eps)
     return last, (last @ lm_head if lm_head is not None else None)
 
 
