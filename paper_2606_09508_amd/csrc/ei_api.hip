@@ -141,7 +141,7 @@ ei_status ei_entropy_probe(const uint16_t* q, const uint16_t* k, ei_dims dims, e
   if (!workspace || workspace_bytes < ei::probe_workspace_bytes(ps))
     return EI_ERR_WORKSPACE;
   if (!aligned16({workspace})) return EI_ERR_UNSUPPORTED;
-  return from_hip(ei::launch_probe(q, k, ps, probe_scale, log_scores, entropy, workspace,
+  return from_hip(ei::launch_probe(q, k, ps, probe_scale, log_scores, entropy, workspace, nullptr,
                                    (hipStream_t)stream));
 }
 
@@ -238,7 +238,7 @@ ei_status ei_sparse_prefill_attn(const uint16_t* q, const uint16_t* k, const uin
   const ei::AttnShape as{(int)z.B, (int)z.Hq, (int)z.Hkv, (int)z.N, tiling.seg_len,
                          tiling.block_len, (int)z.CS, (int)z.CB, kmax, softmax_scale};
   return from_hip(ei::launch_attention(q, k, v, as, ei::kSparse, block_idx, block_cnt, o,
-                                       workspace, (hipStream_t)stream));
+                                       workspace, false, (hipStream_t)stream));
 }
 
 ei_status ei_sparse_prefill_attn_gqa_union(const uint16_t* q, const uint16_t* k,
@@ -309,14 +309,17 @@ ei_status ei_entropy_guided_prefill(const uint16_t* q, const uint16_t* k, const 
   // the probe of one KV group beside the attention of the previous one
   // measured slower: both are bound by vector ALU work, and eight per-group
   // attention launches add their tails.)
+  // The probe's first kernel zeroes the attention's queue counters.
   hipStream_t s0 = (hipStream_t)stream;
-  hipError_t err = ei::launch_probe(q, k, ps, probe_scale, log_scores, entropy, workspace, s0);
+  void* sched = (unsigned char*)workspace + probe_bytes;
+  hipError_t err =
+      ei::launch_probe(q, k, ps, probe_scale, log_scores, entropy, workspace, sched, s0);
   if (err == hipSuccess)
     err = ei::launch_select(log_scores, entropy, ss, head_is_rigid, budget_blocks, block_idx,
                             block_cnt, s0);
   if (err == hipSuccess)
-    err = ei::launch_attention(q, k, v, as, ei::kSparse, block_idx, block_cnt, o,
-                               (unsigned char*)workspace + probe_bytes, s0);
+    err = ei::launch_attention(q, k, v, as, ei::kSparse, block_idx, block_cnt, o, sched,
+                               true, s0);
   return from_hip(err);
 }
 
@@ -334,7 +337,7 @@ ei_status ei_dense_prefill_attn(const uint16_t* q, const uint16_t* k, const uint
                          softmax_scale};
   return from_hip(ei::launch_attention(q, k, v, as,
                                        causal ? ei::kDenseCausal : ei::kDenseFull, nullptr,
-                                       nullptr, o, nullptr, (hipStream_t)stream));
+                                       nullptr, o, nullptr, false, (hipStream_t)stream));
 }
 
 }  // extern "C"

@@ -54,6 +54,7 @@ constexpr int kThreads = 256;
 constexpr int kTileQ = 128;
 constexpr int kSub = 64;            // keys per staged sub-block
 constexpr int kXcds = 8;
+static_assert(kXcds == kSchedCounters, "one queue counter per XCD");
 constexpr unsigned kRotRun = 4;    // tiles a KV group stays on one XCD (static sparse grid)
 constexpr unsigned kRun = 16;      // tile run per XCD when XCDs share a KV group (persistent)
 constexpr unsigned kHeadRun = 16;  // tiles of one query head in a row in an XCD's queue
@@ -224,7 +225,8 @@ __device__ __forceinline__ void plan_item(const XcdPlan& pl, unsigned x, unsigne
 }
 
 // Queue counters of one call (the caller's scheduling workspace), zeroed on
-// the call's stream before the kernel reads them.
+// the call's stream before the kernel reads them (in the one-call path by the
+// probe's first kernel).
 __global__ void sched_reset_kernel(uint32_t* __restrict__ sched) {
   if (threadIdx.x < kXcds) sched[threadIdx.x] = 0u;
 }
@@ -568,16 +570,20 @@ int persistent_grid() {
 template <int MODE, int SUB>
 hipError_t launch_t(const uint16_t* q, const uint16_t* k, const uint16_t* v, const AttnShape& s,
                     const int32_t* bidx, const int32_t* bcnt, uint16_t* o, uint32_t* sched,
-                    hipStream_t stream) {
+                    bool sched_zeroed, hipStream_t stream) {
   const int n_tiles = (s.N + kTileQ - 1) / kTileQ;
   const int64_t total = (int64_t)s.B * s.Hq * n_tiles;
   int64_t grid = (total + kXcds - 1) / kXcds * kXcds;
   XcdPlan plan{};
   int pgrid = 0;
+  // A launch whose items all fit the persistent grid at once has nothing to
+  // queue or steal: the static grid then saves the items' atomics and the
+  // counters' reset (a launch of its own, 4 us, outside the one-call path).
   if (MODE == kSparse && sched != nullptr && make_plan(s, n_tiles, plan) &&
-      (pgrid = persistent_grid()) > 0) {
-    hipLaunchKernelGGL(sched_reset_kernel, dim3(1), dim3(kWave), 0, stream, sched);
-    grid = grid < pgrid ? grid : (int64_t)pgrid;
+      (pgrid = persistent_grid()) > 0 && total > pgrid) {
+    if (!sched_zeroed)
+      hipLaunchKernelGGL(sched_reset_kernel, dim3(1), dim3(kWave), 0, stream, sched);
+    grid = (int64_t)pgrid;
   } else {
     sched = nullptr;
   }
@@ -803,18 +809,20 @@ hipError_t launch_attention_union(const uint16_t* q, const uint16_t* k, const ui
 hipError_t launch_attention(const uint16_t* q, const uint16_t* k, const uint16_t* v,
                             const AttnShape& s, AttnMode mode, const int32_t* block_idx,
                             const int32_t* block_cnt, uint16_t* o, void* sched_ws,
-                            hipStream_t stream) {
+                            bool sched_zeroed, hipStream_t stream) {
   if (s.B * (int64_t)s.Hq * ((s.N + kTileQ - 1) / kTileQ) >= (int64_t)1 << 31)
     return hipErrorInvalidValue;
   uint32_t* sched = (uint32_t*)sched_ws;
   switch (mode) {
     case kSparse:
       return s.Lb == 2 * kSub
-                 ? launch_t<kSparse, 2>(q, k, v, s, block_idx, block_cnt, o, sched, stream)
-                 : launch_t<kSparse, 1>(q, k, v, s, block_idx, block_cnt, o, sched, stream);
+                 ? launch_t<kSparse, 2>(q, k, v, s, block_idx, block_cnt, o, sched, sched_zeroed, stream)
+                 : launch_t<kSparse, 1>(q, k, v, s, block_idx, block_cnt, o, sched, sched_zeroed,
+                                        stream);
     case kDenseCausal:
-      return launch_t<kDenseCausal, 1>(q, k, v, s, nullptr, nullptr, o, nullptr, stream);
-    default: return launch_t<kDenseFull, 1>(q, k, v, s, nullptr, nullptr, o, nullptr, stream);
+      return launch_t<kDenseCausal, 1>(q, k, v, s, nullptr, nullptr, o, nullptr, false, stream);
+    default:
+      return launch_t<kDenseFull, 1>(q, k, v, s, nullptr, nullptr, o, nullptr, false, stream);
   }
 }
 

@@ -118,9 +118,11 @@ size_t probe_workspace_bytes(const ProbeShape& s);
 // Whether the probe kernels support the shape (every validated shape).
 bool probe_supported(const ProbeShape& s);
 
+// sched (or null): the sparse attention's queue counters, zeroed on the
+// way, for an attention launch that follows on the same stream.
 hipError_t launch_probe(const uint16_t* q, const uint16_t* k, const ProbeShape& s,
                         double probe_scale, float* log_scores, float* entropy, void* workspace,
-                        hipStream_t stream);
+                        void* sched, hipStream_t stream);
 
 struct SelectShape {
   int B, Hq, N, Ls, Lb, CS, CB, r, kmax;
@@ -168,11 +170,13 @@ hipError_t launch_attention_union(const uint16_t* q, const uint16_t* k, const ui
                                   const int32_t* block_cnt, uint16_t* o, hipStream_t stream);
 
 // sched_ws: the sparse kernel's scheduling workspace (kAttnSchedBytes, 4-byte
-// aligned) for its persistent grid, or null for the static grid.
+// aligned) for its persistent grid, or null for the static grid; sched_zeroed:
+// its kSchedCounters counters are already zeroed on the stream.
 constexpr size_t kAttnSchedBytes = 256;
+constexpr int kSchedCounters = 8;
 hipError_t launch_attention(const uint16_t* q, const uint16_t* k, const uint16_t* v,
                             const AttnShape& s, AttnMode mode, const int32_t* block_idx,
                             const int32_t* block_cnt, uint16_t* o, void* sched_ws,
-                            hipStream_t stream);
+                            bool sched_zeroed, hipStream_t stream);
 
 }  // namespace ei

@@ -406,11 +406,13 @@ __device__ __forceinline__ void pool_item(const uint16_t* __restrict__ q,
 
 // One wave per item: a query segment (B*Hq*C_S items, the first) or a key
 // block slot (B*Hkv*C_Bt*16 items); item_offset selects where the launch
-// starts (the scores kernel pools the query segments it uses itself).
+// starts (the scores kernel pools the query segments it uses itself).  sched:
+// queue counters of a later launch to zero, or null.
 __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int B, int Hq, int Hkv,
     int N, int Ls, int Lb, int CS, int CB, int CBt, double sgn, unsigned char* __restrict__ ws,
-    Layout lay, int64_t item_offset) {
+    Layout lay, int64_t item_offset, uint32_t* __restrict__ sched) {
+  if (sched != nullptr && blockIdx.x == 0 && threadIdx.x < kSchedCounters) sched[threadIdx.x] = 0u;
   const int lane = threadIdx.x & (kWave - 1);
   const int64_t item = item_offset + (int64_t)blockIdx.x * kPoolWaves + (threadIdx.x >> 6);
   const int64_t nq = (int64_t)B * Hq * CS, nk = (int64_t)B * Hkv * CBt * kTileBlocks;
@@ -907,12 +909,13 @@ constexpr size_t kFusedStaticLds = 2 * kStageBytes;   // stage buffers of the TP
 
 // The key blocks only (the scores kernels pool the query segments).
 hipError_t launch_pool(const uint16_t* q, const uint16_t* k, const ProbeShape& s, double sgn,
-                       unsigned char* ws, const Layout& lay, int CBt, hipStream_t stream) {
+                       unsigned char* ws, const Layout& lay, int CBt, uint32_t* sched,
+                       hipStream_t stream) {
   const int64_t nq = (int64_t)s.B * s.Hq * s.CS;
   const int64_t items = (int64_t)s.B * s.Hkv * CBt * kTileBlocks;
   const int64_t grid = (items + kPoolWaves - 1) / kPoolWaves;
   hipLaunchKernelGGL(pool_kernel, dim3((unsigned)grid), dim3(kPoolThreads), 0, stream, q, k, s.B,
-                     s.Hq, s.Hkv, s.N, s.Ls, s.Lb, s.CS, s.CB, CBt, sgn, ws, lay, nq);
+                     s.Hq, s.Hkv, s.N, s.Ls, s.Lb, s.CS, s.CB, CBt, sgn, ws, lay, nq, sched);
   return hipGetLastError();
 }
 
@@ -942,12 +945,12 @@ bool probe_select_supported(const ProbeShape& s) {
 
 hipError_t launch_probe(const uint16_t* q, const uint16_t* k, const ProbeShape& s,
                         double probe_scale, float* log_scores, float* entropy, void* workspace,
-                        hipStream_t stream) {
+                        void* sched, hipStream_t stream) {
   const Layout lay = layout(s);
   unsigned char* ws = (unsigned char*)workspace;
   const int CBt = (s.CB + kTileBlocks - 1) / kTileBlocks;
   const double sgn = probe_scale > 0.0 ? 1.0 : (probe_scale < 0.0 ? -1.0 : 0.0);
-  hipError_t e = launch_pool(q, k, s, sgn, ws, lay, CBt, stream);
+  hipError_t e = launch_pool(q, k, s, sgn, ws, lay, CBt, (uint32_t*)sched, stream);
   if (e != hipSuccess) return e;
   const int G = s.Hq / s.Hkv;
   const int n_groups = s.B * s.Hkv;
@@ -971,7 +974,7 @@ hipError_t launch_probe_select(const uint16_t* q, const uint16_t* k, const Probe
   unsigned char* ws = (unsigned char*)workspace;
   const int CBt = (s.CB + kTileBlocks - 1) / kTileBlocks;
   const double sgn = probe_scale > 0.0 ? 1.0 : (probe_scale < 0.0 ? -1.0 : 0.0);
-  hipError_t e = launch_pool(q, k, s, sgn, ws, lay, CBt, stream);
+  hipError_t e = launch_pool(q, k, s, sgn, ws, lay, CBt, nullptr, stream);
   if (e != hipSuccess) return e;
   const int G = s.Hq / s.Hkv;
   const int n_groups = s.B * s.Hkv;
