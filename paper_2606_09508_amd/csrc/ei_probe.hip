@@ -328,30 +328,17 @@ __device__ __forceinline__ void pool_item(const uint16_t* __restrict__ q,
 #pragma unroll
       for (int u = 0; u < 16; ++u)
         w[u] = load_nt16(base + (size_t)(r + 4 * u) * kHeadDim + 8 * c);
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const uint32_t ww[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float lo = bf16_lo(ww[e]), hi = bf16_hi(ww[e]);
-          mx[2 * e] = fmaxf(mx[2 * e], lo);
-          mn[2 * e] = fminf(mn[2 * e], lo);
-          mx[2 * e + 1] = fmaxf(mx[2 * e + 1], hi);
-          mn[2 * e + 1] = fminf(mn[2 * e + 1], hi);
-        }
-      }
+      fold_rows<16>(w, mx, mn);
     }
-    for (; r < rows; r += 4) {
-      const uint4 w = *(const uint4*)(base + (size_t)r * kHeadDim + 8 * c);
-      const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+    // the rows left over as one batch, repeating the last row (a max or min
+    // is not moved by it): one round trip, where a loop over single rows took
+    // up to 16
+    if (r < rows) {
+      uint4 w[16];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float lo = bf16_lo(ww[e]), hi = bf16_hi(ww[e]);
-        mx[2 * e] = fmaxf(mx[2 * e], lo);
-        mn[2 * e] = fminf(mn[2 * e], lo);
-        mx[2 * e + 1] = fmaxf(mx[2 * e + 1], hi);
-        mn[2 * e + 1] = fminf(mn[2 * e + 1], hi);
-      }
+      for (int u = 0; u < 16; ++u)
+        w[u] = load_nt16(base + (size_t)min(r + 4 * u, rows - 1) * kHeadDim + 8 * c);
+      fold_rows<16>(w, mx, mn);
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -425,12 +412,13 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
 // Logits, softmax statistics, ln A and the entropy
 // ---------------------------------------------------------------------------
 
-constexpr int kThreads = 256;                       // 4 waves
-// One row tile (4 units) per wave, 16 units per workgroup.  Two row tiles
-// per wave share each staged key tile over twice the rows but need ~190
-// VGPRs (2 waves per SIMD against 4): 5% slower on the 128k layer.
+// One row tile (4 units) per wave, kWaves waves (16 units) per workgroup
+// sharing each staged key tile.  Two row tiles per wave share it over twice
+// the rows but need ~190 VGPRs (2 waves per SIMD against 4): 5% slower on the
+// 128k layer.  Launches that would leave CUs idle take one-wave workgroups
+// (kSmallWaves; the rule is at launch_probe).
 constexpr int KT = 1;
-constexpr int kWaves = kThreads / kWave;
+constexpr int kWaves = 4, kSmallWaves = 1;
 constexpr int kUnits = kWaves * 4 * KT;
 constexpr int kStageBytes = kKLimbTile + kKMetaTile;
 constexpr int kTilesPerStep = 2;    // key tiles staged per barrier
@@ -471,8 +459,8 @@ __device__ __forceinline__ double limb_logit(const i32x4 (&acc)[2][2], int a, in
   return fma((double)p11, sk14, (double)x * sk);
 }
 
-template <int MODE, int TPS, int SLOTS>
-__global__ __launch_bounds__(kThreads, MODE == kScoresSelect ? 1 : 4) void scores_kernel(
+template <int MODE, int TPS, int SLOTS, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void scores_kernel(
     const uint16_t* __restrict__ qsrc, int B, int N, int Ls, int Lb,
     unsigned char* __restrict__ ws, Layout lay, float* __restrict__ log_scores,
     float* __restrict__ entropy, int Hq, int Hkv, int CS, int CB, int CBt, int r, int n_groups,
@@ -480,6 +468,9 @@ __global__ __launch_bounds__(kThreads, MODE == kScoresSelect ? 1 : 4) void score
     const int32_t* __restrict__ kblocks, int32_t* __restrict__ idx, int32_t* __restrict__ cnt,
     int kmax, int row_cap) {
   constexpr int kTilesPerStep = TPS;
+  constexpr int kThreads = WAVES * kWave, kUnits = WAVES * 4 * KT;
+  // one-wave workgroups find their query segments pooled by pool_kernel
+  constexpr bool kPoolsQ = MODE != kScoresSelect && WAVES == kWaves;
   __shared__ __attribute__((aligned(16))) unsigned char stage[2][kTilesPerStep * kStageBytes];
   // kScoresSelect: kUnits rows of row_cap scores (dynamic LDS)
   extern __shared__ __attribute__((aligned(16))) float rows_lds[];
@@ -517,7 +508,7 @@ __global__ __launch_bounds__(kThreads, MODE == kScoresSelect ? 1 : 4) void score
   // HBM reads overlap the logits of the CU's other workgroups; the key blocks
   // are pooled beforehand by pool_kernel.  kScoresSelect reads the records
   // its kScoresEntropy launch wrote.
-  if constexpr (MODE != kScoresSelect) {
+  if constexpr (kPoolsQ) {
     const int uw = u0 + 4 * KT * __builtin_amdgcn_readfirstlane(wave);
     // whole segments: L_S = 128 and the wave's last unit's segment ends by N
     if (KT == 1 && Ls == 128 && uw + 3 < U && (int64_t)((uw + 3) / G + 1) * 128 <= N) {
@@ -646,15 +637,16 @@ __global__ __launch_bounds__(kThreads, MODE == kScoresSelect ? 1 : 4) void score
   // Key tile staging: two LDS buffers of kTilesPerStep tiles each, the next
   // step's tiles held in registers (a slot past the last tile repeats the
   // last tile, unread).
-  i32x4 p0[kTilesPerStep], p1[kTilesPerStep], pm[kTilesPerStep];
+  constexpr int kPer = kKLimbTile / 16 / kThreads;   // 16-byte chunks of a tile per thread
+  i32x4 pl[kTilesPerStep][kPer], pm[kTilesPerStep];
   const int n_steps = (nt + kTilesPerStep - 1) / kTilesPerStep;
   auto load_step = [&](int i) {
 #pragma unroll
     for (int k = 0; k < kTilesPerStep; ++k) {
       const int t = min(kTilesPerStep * i + k, nt - 1);
       const i32x4* src = (const i32x4*)(klimb + (size_t)t * kKLimbTile);
-      p0[k] = src[tid];
-      p1[k] = src[kThreads + tid];
+#pragma unroll
+      for (int c = 0; c < kPer; ++c) pl[k][c] = src[c * kThreads + tid];
       if (tid < kKMetaTile / 16) pm[k] = ((const i32x4*)(kmeta + (size_t)t * kKMetaTile))[tid];
     }
   };
@@ -662,8 +654,8 @@ __global__ __launch_bounds__(kThreads, MODE == kScoresSelect ? 1 : 4) void score
 #pragma unroll
     for (int k = 0; k < kTilesPerStep; ++k) {
       i32x4* dst = (i32x4*)(stage[buf] + k * kStageBytes);
-      dst[tid] = p0[k];
-      dst[kThreads + tid] = p1[k];
+#pragma unroll
+      for (int c = 0; c < kPer; ++c) dst[c * kThreads + tid] = pl[k][c];
       if (tid < kKMetaTile / 16) dst[kKLimbTile / 16 + tid] = pm[k];
     }
   };
@@ -869,7 +861,7 @@ __global__ __launch_bounds__(kThreads, MODE == kScoresSelect ? 1 : 4) void score
     // Top-k of each of the wave's units from its LDS row (written by this
     // wave; the barrier above ordered the writes), with the stage buffers,
     // free after that barrier, as the selection's histogram and candidates.
-    static_assert(kWaves * (topk::kHistWords + topk::kCandWords) * 4 <= sizeof(stage),
+    static_assert(WAVES * (topk::kHistWords + topk::kCandWords) * 4 <= sizeof(stage),
                   "top-k scratch must fit the stage buffers");
     const int wv = __builtin_amdgcn_readfirstlane(wave);
     uint32_t* hist = (uint32_t*)&stage[0][0] + wv * (topk::kHistWords + topk::kCandWords);
@@ -907,15 +899,17 @@ size_t fused_lds_bytes(const ProbeShape& s) { return (size_t)kUnits * fused_row_
 constexpr size_t kLdsBytes = 160 * 1024;
 constexpr size_t kFusedStaticLds = 2 * kStageBytes;   // stage buffers of the TPS = 1 instance
 
-// The key blocks only (the scores kernels pool the query segments).
+// The key blocks, and with pool_q the query segments (else the scores kernel
+// pools them).
 hipError_t launch_pool(const uint16_t* q, const uint16_t* k, const ProbeShape& s, double sgn,
                        unsigned char* ws, const Layout& lay, int CBt, uint32_t* sched,
-                       hipStream_t stream) {
+                       bool pool_q, hipStream_t stream) {
   const int64_t nq = (int64_t)s.B * s.Hq * s.CS;
-  const int64_t items = (int64_t)s.B * s.Hkv * CBt * kTileBlocks;
+  const int64_t items = (int64_t)s.B * s.Hkv * CBt * kTileBlocks + (pool_q ? nq : 0);
   const int64_t grid = (items + kPoolWaves - 1) / kPoolWaves;
   hipLaunchKernelGGL(pool_kernel, dim3((unsigned)grid), dim3(kPoolThreads), 0, stream, q, k, s.B,
-                     s.Hq, s.Hkv, s.N, s.Ls, s.Lb, s.CS, s.CB, CBt, sgn, ws, lay, nq, sched);
+                     s.Hq, s.Hkv, s.N, s.Ls, s.Lb, s.CS, s.CB, CBt, sgn, ws, lay, pool_q ? 0 : nq,
+                     sched);
   return hipGetLastError();
 }
 
@@ -924,16 +918,62 @@ hipError_t launch_fused_select(const ProbeShape& s, const Layout& lay, unsigned 
                                int CBt, int n_groups, int n_chunks, double ps_abs, double sgn,
                                float tau, const int32_t* kblocks, int32_t* idx, int32_t* cnt,
                                int kmax, hipStream_t stream) {
-  auto kern = scores_kernel<kScoresSelect, 1, SLOTS>;
+  auto kern = scores_kernel<kScoresSelect, 1, SLOTS, kWaves>;
   const size_t lds = fused_lds_bytes(s);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)n_groups * n_chunks)), dim3(kThreads), lds,
-                     stream, nullptr, s.B, s.N, s.Ls, s.Lb, ws, lay, nullptr, nullptr, s.Hq, s.Hkv,
+  hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)n_groups * n_chunks)),
+                     dim3(kWaves * kWave), lds, stream, nullptr, s.B, s.N, s.Ls, s.Lb, ws, lay, nullptr, nullptr, s.Hq, s.Hkv,
                      s.CS, s.CB, CBt, s.r,
                      n_groups, n_chunks, ps_abs, sgn, tau, (UnitStats*)(ws + lay.stats), kblocks,
                      idx, cnt, kmax, fused_row_cap(s));
+  return hipGetLastError();
+}
+
+// Pooling, then ln A and the entropies (kScoresWrite) or the entropies and
+// statistics (kScoresEntropy).
+//
+// A launch of at most kSmallGrid 16-unit workgroups (half the chip's 256 CUs;
+// three eighths if its rows are longer than kSmallRow blocks, which gain more
+// from key tiles shared by four waves) leaves most of the chip idle while each of its waves pools four segments in
+// turn: the query segments are then pooled by pool_kernel, a wave each, and
+// the scores kernel takes one-wave workgroups of 4 units.  Probe alone, 16-unit
+// against one-wave workgroups: 2 workgroups (4 heads, 1024 tokens) 22.3 / 16.4
+// us, 32 (32 heads, 2047 tokens) 46.1 / 19.0, 64 (3999) 33.4 / 20.2, 128 (8192)
+// 36.8 / 33.3, 64 (4 heads, 32768) 59.4 / 51.3; but 128 (4 heads, 65536) 96.6 /
+// 97.6, 224 (28 heads, 16384) 48.3 / 54.0 and 256 (32 heads, 16384) 55.0 /
+// 59.6: from there the separate pass over Q and the unshared key tiles cost
+// more.
+constexpr int64_t kSmallGrid = 128, kSmallGridLong = 96;
+constexpr int kSmallRow = 256;
+template <int MODE>
+hipError_t launch_pool_scores(const uint16_t* q, const uint16_t* k, const ProbeShape& s,
+                              double probe_scale, const Layout& lay, unsigned char* ws,
+                              float* log_scores, float* entropy, uint32_t* sched,
+                              hipStream_t stream) {
+  const int CBt = (s.CB + kTileBlocks - 1) / kTileBlocks;
+  const double sgn = probe_scale > 0.0 ? 1.0 : (probe_scale < 0.0 ? -1.0 : 0.0);
+  const double ps_abs = fabs(probe_scale);
+  // skip the residual MFMA where it moves no logit by 2^-30 or more
+  const float tau = probe_scale == 0.0 ? INFINITY : (float)(0x1p-30 / ps_abs);
+  const int64_t n_groups = (int64_t)s.B * s.Hkv, U = (int64_t)(s.Hq / s.Hkv) * s.CS;
+  const bool small = n_groups * ((U + kUnits - 1) / kUnits) <=
+                     (s.CB <= kSmallRow ? kSmallGrid : kSmallGridLong);
+  hipError_t e = launch_pool(q, k, s, sgn, ws, lay, CBt, sched, small, stream);
+  if (e != hipSuccess) return e;
+  auto launch = [&](auto kern, int waves) {
+    const int n_chunks = (int)((U + 4 * KT * waves - 1) / (4 * KT * waves));
+    hipLaunchKernelGGL(kern, dim3((unsigned)(n_groups * n_chunks)), dim3(waves * kWave), 0, stream,
+                       q, s.B, s.N, s.Ls, s.Lb, ws, lay, log_scores, entropy, s.Hq, s.Hkv, s.CS,
+                       s.CB, CBt, s.r, (int)n_groups, n_chunks, ps_abs, sgn, tau,
+                       MODE == kScoresEntropy ? (UnitStats*)(ws + lay.stats) : nullptr, nullptr,
+                       nullptr, nullptr, 0, 0);
+  };
+  if (small)
+    launch(scores_kernel<MODE, 1, 1, kSmallWaves>, kSmallWaves);
+  else
+    launch(scores_kernel<MODE, kTilesPerStep, 1, kWaves>, kWaves);
   return hipGetLastError();
 }
 
@@ -946,24 +986,9 @@ bool probe_select_supported(const ProbeShape& s) {
 hipError_t launch_probe(const uint16_t* q, const uint16_t* k, const ProbeShape& s,
                         double probe_scale, float* log_scores, float* entropy, void* workspace,
                         void* sched, hipStream_t stream) {
-  const Layout lay = layout(s);
-  unsigned char* ws = (unsigned char*)workspace;
-  const int CBt = (s.CB + kTileBlocks - 1) / kTileBlocks;
-  const double sgn = probe_scale > 0.0 ? 1.0 : (probe_scale < 0.0 ? -1.0 : 0.0);
-  hipError_t e = launch_pool(q, k, s, sgn, ws, lay, CBt, (uint32_t*)sched, stream);
-  if (e != hipSuccess) return e;
-  const int G = s.Hq / s.Hkv;
-  const int n_groups = s.B * s.Hkv;
-  const int n_chunks = (G * s.CS + kUnits - 1) / kUnits;
-  const double ps_abs = fabs(probe_scale);
-  // skip the residual MFMA where it moves no logit by 2^-30 or more
-  const float tau = probe_scale == 0.0 ? INFINITY : (float)(0x1p-30 / ps_abs);
-  hipLaunchKernelGGL((scores_kernel<kScoresWrite, kTilesPerStep, 1>),
-                     dim3((unsigned)((int64_t)n_groups * n_chunks)), dim3(kThreads), 0, stream,
-                     q, s.B, s.N, s.Ls, s.Lb, ws, lay, log_scores, entropy, s.Hq, s.Hkv, s.CS,
-                     s.CB, CBt, s.r, n_groups,
-                     n_chunks, ps_abs, sgn, tau, nullptr, nullptr, nullptr, nullptr, 0, 0);
-  return hipGetLastError();
+  return launch_pool_scores<kScoresWrite>(q, k, s, probe_scale, layout(s),
+                                          (unsigned char*)workspace, log_scores, entropy,
+                                          (uint32_t*)sched, stream);
 }
 
 hipError_t launch_probe_select(const uint16_t* q, const uint16_t* k, const ProbeShape& s,
@@ -974,21 +999,14 @@ hipError_t launch_probe_select(const uint16_t* q, const uint16_t* k, const Probe
   unsigned char* ws = (unsigned char*)workspace;
   const int CBt = (s.CB + kTileBlocks - 1) / kTileBlocks;
   const double sgn = probe_scale > 0.0 ? 1.0 : (probe_scale < 0.0 ? -1.0 : 0.0);
-  hipError_t e = launch_pool(q, k, s, sgn, ws, lay, CBt, nullptr, stream);
-  if (e != hipSuccess) return e;
-  const int G = s.Hq / s.Hkv;
   const int n_groups = s.B * s.Hkv;
-  const int n_chunks = (G * s.CS + kUnits - 1) / kUnits;
+  const int n_chunks = (s.Hq / s.Hkv * s.CS + kUnits - 1) / kUnits;
   const double ps_abs = fabs(probe_scale);
   const float tau = probe_scale == 0.0 ? INFINITY : (float)(0x1p-30 / ps_abs);
   // entropies and each unit's statistics, no ln A
-  hipLaunchKernelGGL((scores_kernel<kScoresEntropy, kTilesPerStep, 1>),
-                     dim3((unsigned)((int64_t)n_groups * n_chunks)), dim3(kThreads), 0, stream,
-                     q, s.B, s.N, s.Ls, s.Lb, ws, lay, nullptr, entropy, s.Hq, s.Hkv, s.CS,
-                     s.CB, CBt, s.r, n_groups,
-                     n_chunks, ps_abs, sgn, tau, (UnitStats*)(ws + lay.stats), nullptr, nullptr,
-                     nullptr, 0, 0);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipError_t e = launch_pool_scores<kScoresEntropy>(q, k, s, probe_scale, lay, ws, nullptr,
+                                                    entropy, nullptr, stream);
+  if (e != hipSuccess) return e;
   // classification and budgets (Algorithm 3) from the entropies
   if ((e = launch_budget(entropy, ss, rigid, budget_blocks, stream)) != hipSuccess) return e;
   // ln A again, into LDS, and the top-k from there

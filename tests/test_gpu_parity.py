@@ -141,6 +141,27 @@ def test_path_parity_small(case, seed):
     say(f"  entropy rel {hrel:.2e}  logscore abs {lerr:.2e}  attn max {amax:.2e} mean {amean:.2e}")
 
 
+@pytest.mark.parametrize("wl,case", [
+    ("c2", dict(N=8192)),                         # 128 16-unit workgroups: one-wave workgroups
+    ("c2", dict(N=8192 - 63)),                    # the same, a ragged last segment and block
+    ("c2", dict(N=8192 + 65)),                    # 136: four-wave workgroups, ragged
+    ("c2", dict(N=8192 + 256)),                   # the same, whole segments
+    ("c4", dict(N=10240 - 1, n_spans=2)),         # 140, G = 7, residual tiles
+    ("c4", dict(N=4096 + 33, n_spans=2)),         # 60, G = 7, residual tiles
+    ("c2", dict(N=16384 + 192, Ls=256, Lb=128)),  # 136, longer segments and blocks
+    ("c2", dict(N=16384 - 60, Ls=256, Lb=64)),    # 128
+], ids=lambda x: x if isinstance(x, str) else ",".join(f"{k}={v}" for k, v in x.items()))
+def test_probe_workgroup_sizes(wl, case):
+    """Both workgroup sizes of the scores kernel at the edge of the rule that
+    picks one, with whole and ragged last segments and blocks: every row's
+    ln A and entropy against the oracle."""
+    w = synth.make(wl, 12, **case)
+    ls, en = eb.entropy_probe(to_dev(w.q), to_dev(w.k), w.Ls, w.Lb, w.probe_scale)
+    torch.cuda.synchronize()
+    hrel, lerr = check_probe(w, {"ls": ls.cpu().numpy(), "en": en.cpu().numpy()})
+    say(f"[probe {wl} {case}] entropy rel {hrel:.2e} L {lerr:.2e}")
+
+
 def _span_inputs(N=1024, Hq=4, Hkv=1, seed=11):
     """Query / key elements far below each pooled vector's maximum, so that
     the probe's fixed-point grid (2^-13 of the maximum's binade) leaves
