@@ -22,6 +22,7 @@
 //                 binary64 with FP contraction off, in the order the budget
 //                 recurrence is written, so the result is bit-identical to any
 //                 other IEEE evaluation in that order.
+//  select_short_kernel  both for layers of at most 64 segments
 //  topk_kernel    one wave per (b, h, s) row, reading the row's ln A from
 //                 HBM; the selection itself (radix select of the k-th largest
 //                 score, ties to the highest block index, ascending output)
@@ -189,6 +190,77 @@ __global__ __launch_bounds__(kThreads) void budget_kernel(
 
 constexpr int kWavesPerGroup = kThreads / kWave;
 
+// What a top-k wave needs to form its row's budget itself (select_short_kernel).
+struct BudgetArgs {
+  const float* entropy;
+  int Hq, G, Lb, Bh, mult, mode;
+  float e_t;
+  double alpha, delta_t;
+  uint8_t* rigid;
+  int32_t* k_out;
+};
+
+// k_s of row (bh, s) of a layer of at most kWave segments, by the whole wave
+// (bh, s wave-uniform): lane l holds segment l's entropy and increment, and
+// the recurrence runs up to s in its own order, as in budget_kernel.
+template <bool GROUP>
+__device__ __forceinline__ int row_budget(const BudgetArgs& p, int64_t bh, int s, int CS, int r,
+                                          int lane) {
+  const float* e = p.entropy + (GROUP ? bh - (bh % p.Hq) % p.G : bh) * CS;
+  const int l = min(lane, CS - 1);
+  float es;
+  if constexpr (!GROUP) {
+    es = e[l];
+  } else {
+    double sum = 0.0;
+    for (int h = 0; h < p.G; ++h) sum += (double)e[(int64_t)h * CS + l];
+    es = (float)(sum / (double)p.G);
+  }
+  const double B0 = (double)p.Bh, cap = (double)p.mult * B0;
+  const bool below = __builtin_amdgcn_ballot_w64(!(es < p.e_t)) == 0;   // every segment
+  double x = B0;
+  if (!below) {
+    const double ep = (double)__shfl_up(es, 1), ec = (double)es;
+    const double num = fabs(ec - ep);
+    const double ratio = (num == 0.0 && ep == 0.0) ? 0.0 : num / ep;
+    double d = (p.alpha * B0) * (ratio - p.delta_t);
+    d = (lane == 0 || (p.mode == EI_CLASSIFY_SEGMENT && es < p.e_t)) ? -INFINITY : d;
+    const int2 w = __builtin_bit_cast(int2, d);
+    for (int i = 0; i <= s; ++i) {
+      const double di = __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(w.x, i),
+                                                             __builtin_amdgcn_readlane(w.y, i)));
+      x = fmin(fmax(x + di, B0), cap);
+    }
+  }
+  const int k = (int)min((int64_t)floor(x / (double)p.Lb), (int64_t)s * r);
+  if (lane == 0) {
+    p.k_out[bh * CS + s] = k;
+    if (s == 0) p.rigid[bh] = (uint8_t)(below ? 1 : 0);
+  }
+  return __builtin_amdgcn_readfirstlane(k);
+}
+
+// Layers of at most kWave segments whose rows fit the 8-slot selector: budget
+// and top-k in one launch, each row's wave running its head's recurrence up to
+// its segment (at most 64 steps, ~1 us) where a launch of its own for the
+// budgets costs 4.7 us.
+template <bool GROUP>
+__global__ __launch_bounds__(kThreads, 8) void select_short_kernel(
+    const float* __restrict__ log_scores, BudgetArgs p, int64_t rows, int CS, int CB, int r,
+    int kmax, int32_t* __restrict__ idx, int32_t* __restrict__ cnt) {
+  __shared__ __attribute__((aligned(16))) uint32_t hist_all[kWavesPerGroup][topk::kHistWords];
+  __shared__ uint32_t cand_all[kWavesPerGroup][topk::kCandWords];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
+  const int64_t row = (int64_t)blockIdx.x * kWavesPerGroup + wv;
+  if (row >= rows) return;   // no workgroup barriers below
+  const int lane = threadIdx.x & (kWave - 1);
+  const int s = (int)(row % CS);
+  const int kk = row_budget<GROUP>(p, row / CS, s, CS, r, lane);
+  const float* L = log_scores + row * (int64_t)CB;
+  topk::select_row<8>([&](int j) { return L[j]; }, CB, s, r, CB, kmax, kk,
+                      idx + row * (int64_t)kmax, cnt + row, hist_all[wv], cand_all[wv], lane);
+}
+
 template <int SLOTS>
 __global__ __launch_bounds__(kThreads, SLOTS <= 16 ? 8 : SLOTS <= 32 ? 6 : 1) void topk_kernel(
     const float* __restrict__ log_scores, const int32_t* __restrict__ kblocks, int64_t rows,
@@ -239,9 +311,22 @@ hipError_t launch_budget(const float* entropy, const SelectShape& s, uint8_t* ri
 hipError_t launch_select(const float* log_scores, const float* entropy, const SelectShape& s,
                          uint8_t* rigid, int32_t* budget_blocks, int32_t* block_idx,
                          int32_t* block_cnt, hipStream_t stream) {
+  const int npast_max = (s.CS - 1) * s.r;
+  if (s.CS <= kWave && npast_max <= 8 * kWave) {
+    const BudgetArgs p{entropy, s.Hq, s.G, s.Lb, s.Bh, s.mult, s.mode, s.e_t, s.alpha, s.delta_t,
+                       rigid, budget_blocks};
+    const int64_t rows = (int64_t)s.B * s.Hq * s.CS;
+    const dim3 grid((unsigned)((rows + kWavesPerGroup - 1) / kWavesPerGroup));
+    if (s.mode == EI_CLASSIFY_GQA_GROUP)
+      hipLaunchKernelGGL(select_short_kernel<true>, grid, dim3(kThreads), 0, stream, log_scores, p,
+                         rows, s.CS, s.CB, s.r, s.kmax, block_idx, block_cnt);
+    else
+      hipLaunchKernelGGL(select_short_kernel<false>, grid, dim3(kThreads), 0, stream, log_scores,
+                         p, rows, s.CS, s.CB, s.r, s.kmax, block_idx, block_cnt);
+    return hipGetLastError();
+  }
   hipError_t e = launch_budget(entropy, s, rigid, budget_blocks, stream);
   if (e != hipSuccess) return e;
-  const int npast_max = (s.CS - 1) * s.r;
   if (npast_max <= 8 * kWave)
     return launch_topk_t<8>(log_scores, budget_blocks, s, block_idx, block_cnt, stream);
   if (npast_max <= 16 * kWave)
