@@ -570,9 +570,8 @@ __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void 
   // The residual part of the 16 logits per row of tile kt and key tile t, if
   // its bound can reach tau: bf16 MFMA with rows (unit, vector, 0 / pad) and
   // the operand [q_r | q_g] . [k | k_r].  corr[bk][2 a] is the lane's value.
-  // A half whose bound is zero (no residual bits in the row tile's query
-  // vectors, or in the tile's key vectors) only adds exact zeros and is
-  // skipped; do_q / do_k are wave-uniform.
+  // A half that can only move a logit by less than tau / 2 is left out;
+  // do_q / do_k are wave-uniform.
   auto residual = [&](int kt, int t, f32x4 (&corr)[2], bool do_q, bool do_k) {
     corr[0] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     corr[1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -625,8 +624,14 @@ __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void 
     }
     if (__builtin_amdgcn_ballot_w64(need) != 0) {
       f32x4 corr[2];
-      residual(kt, t, corr, __builtin_amdgcn_ballot_w64(Rqm[kt] > 0.0f) != 0,
-               __builtin_amdgcn_ballot_w64(k0.R > 0.0f || k1.R > 0.0f) != 0);
+      // A half is formed where its own bound passes tau / 2: the halves left
+      // out together still move a logit by less than tau.  (Gated on R > 0, a
+      // residual of 1e-13 in one element pulled in a whole half: 28 heads,
+      // 65536 tokens, spread key norms 458 us, now 316.)
+      const float half = 0.5f * tau;
+      residual(kt, t, corr,
+               __builtin_amdgcn_ballot_w64(fmaxf(k0.A, k1.A) * Rqm[kt] > half) != 0,
+               __builtin_amdgcn_ballot_w64(fmaxf(k0.R, k1.R) * Aqm[kt] > half) != 0);
 #pragma unroll
       for (int a = 0; a < 2; ++a)
 #pragma unroll
