@@ -87,74 +87,92 @@ __device__ __forceinline__ int swz_v(int row, int chunk) {
   return chunk ^ ((0xAC60 >> (4 * (row & 3))) & 15);
 }
 
-// 16 bytes per lane from global memory straight into LDS at lds_base + 16 *
-// lane (global_load_lds_dwordx4; M0 holds the LDS base and is restored).
-// Written as asm so that the compiler does not treat the copy as a pending
-// LDS write before every later LDS read: completion is enforced explicitly
-// with a vmcnt wait before the barrier that publishes a stage.
-__device__ __forceinline__ void copy16_to_lds(const uint16_t* src, uint32_t lds_base) {
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %2, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "s"(lds_base), "v"(src)
-      : "memory");
+// NC copies of 16 bytes per lane from global memory straight into LDS
+// (global_load_lds_dwordx4: lane l's bytes land at M0 + 16 l), from a
+// wave-uniform base (SGPR pair) and 32-bit lane offsets, each 1 KB further on
+// than the last in memory and in LDS: the instruction's offset moves both
+// addresses, so M0 is set once.  Written as asm so that the compiler does not
+// treat a copy as a pending LDS write before every later LDS read: completion
+// is enforced explicitly with a vmcnt wait before the barrier that publishes a
+// stage.
+template <int NC>
+__device__ __forceinline__ void copy_rows_to_lds(const unsigned char* sbase, const uint32_t* off,
+                                                 uint32_t lds_base) {
+  static_assert(NC == 2 || NC == 4, "copies of a wave per stage and tensor");
+  if constexpr (NC == 4)
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %5\n\t"
+        "global_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+        "global_load_lds_dwordx4 %3, %5 offset:2048\n\t"
+        "global_load_lds_dwordx4 %4, %5 offset:3072"
+        :
+        : "s"(lds_base), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(sbase)
+        : "memory", "m0");
+  else
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %3\n\t"
+        "global_load_lds_dwordx4 %2, %3 offset:1024"
+        :
+        : "s"(lds_base), "v"(off[0]), "v"(off[1]), "s"(sbase)
+        : "memory", "m0");
 }
 
-// The same copy with the global address formed as a wave-uniform base (SGPR
-// pair) plus a 32-bit lane offset, so that issuing it takes no vector
-// arithmetic (M0 restored as above).
-__device__ __forceinline__ void copy16_to_lds_s(const unsigned char* sbase, uint32_t voff,
+// One such copy.
+__device__ __forceinline__ void copy_row_to_lds(const unsigned char* sbase, uint32_t off,
                                                 uint32_t lds_base) {
-  uint32_t saved;
   asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
+      "s_mov_b32 m0, %0\n\t"
       "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %2, %3\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "s"(lds_base), "v"(voff), "s"(sbase)
-      : "memory");
+      "global_load_lds_dwordx4 %1, %2"
+      :
+      : "s"(lds_base), "v"(off), "s"(sbase)
+      : "memory", "m0");
 }
 
-// Global -> LDS without registers: each wave moves 16 rows of K and 16 rows
-// of V (4 + 4 instructions of 64 lanes x 16 bytes).  Lane L of instruction j
-// fills row 16 w + 4 j + L / 16, swizzled chunk position L % 16; koff / voff
-// hold those rows' byte offsets inside a block.  Rows at or past N are read
-// from row N - 1 (finite data whose scores are masked).
+// Global -> LDS without registers: each of 16 / NC waves moves 4 NC rows of K
+// and of V (NC + NC instructions of 64 lanes x 16 bytes).  Lane L of
+// instruction j fills row 4 NC w + 4 j + L / 16, swizzled chunk position
+// L % 16.  koff holds those K rows' byte offsets inside a block less the
+// 1024 j of the instruction's offset, voff the same for V (one value: its
+// swizzle repeats every 4 rows).  Rows at or past N are read from row N - 1
+// (finite data whose scores are masked).
+template <int NC>
 __device__ __forceinline__ void issue_stage(unsigned char* stage, const uint16_t* __restrict__ kh,
                                             const uint16_t* __restrict__ vh, int k0, int N,
                                             int wave, int lane, const uint32_t* koff,
-                                            const uint32_t* voff) {
-  const int pos = lane & 15;
-  const uint32_t base = (uint32_t)(uintptr_t)stage;
+                                            uint32_t voff) {
+  const uint32_t dst = (uint32_t)(uintptr_t)stage +
+                       (uint32_t)(4 * NC * __builtin_amdgcn_readfirstlane(wave) * kRowBytes);
+  const unsigned char* kb = (const unsigned char*)kh + (size_t)k0 * kRowBytes;
+  const unsigned char* vb = (const unsigned char*)vh + (size_t)k0 * kRowBytes;
   if (k0 + kSub <= N) {   // whole block inside the sequence
-    const unsigned char* kb = (const unsigned char*)kh + (size_t)k0 * kRowBytes;
-    const unsigned char* vb = (const unsigned char*)vh + (size_t)k0 * kRowBytes;
-    const uint32_t dst0 =
-        base + (uint32_t)(16 * __builtin_amdgcn_readfirstlane(wave) * kRowBytes);
+    copy_rows_to_lds<NC>(kb, koff, dst);
+    uint32_t vo[NC];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      copy16_to_lds_s(kb, koff[j], dst0 + 4 * j * kRowBytes);
-      copy16_to_lds_s(vb, voff[j], dst0 + 4 * j * kRowBytes + kTileBytes);
-    }
+    for (int j = 0; j < NC; ++j) vo[j] = voff;
+    copy_rows_to_lds<NC>(vb, vo, dst + kTileBytes);
     return;
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = 16 * wave + 4 * j + (lane >> 4);
-    const int grow = min(k0 + row, N - 1);
-    const size_t roff = (size_t)grow * kHeadDim;
-    const uint32_t dst = base + (uint32_t)((16 * wave + 4 * j) * kRowBytes);
-    copy16_to_lds(kh + roff + 8 * swz(row, pos), __builtin_amdgcn_readfirstlane(dst));
-    copy16_to_lds(vh + roff + 8 * swz_v(row, pos),
-                  __builtin_amdgcn_readfirstlane(dst + kTileBytes));
+  for (int j = 0; j < NC; ++j) {   // the block that holds the sequence's end
+    const int row = 4 * NC * wave + 4 * j + (lane >> 4), pos = lane & 15;
+    const uint32_t roff = (uint32_t)(min(row, N - 1 - k0) * kRowBytes);
+    copy_row_to_lds(kb, roff + 16 * swz(row, pos), dst + 1024 * j);
+    copy_row_to_lds(vb, roff + 16 * swz_v(row, pos), dst + 1024 * j + kTileBytes);
   }
+}
+
+template <int NC>
+__device__ __forceinline__ void stage_offsets(int wave, int lane, uint32_t* koff, uint32_t& voff) {
+  const int row = 4 * NC * wave + (lane >> 4);
+#pragma unroll
+  for (int j = 0; j < NC; ++j)
+    koff[j] = (uint32_t)(row * kRowBytes + 16 * swz(row + 4 * j, lane & 15));
+  voff = (uint32_t)(row * kRowBytes + 16 * swz_v(row, lane & 15));
 }
 
 // K operand of S^T = K Q^T: 8 bf16 of key row `row`, dims 16 s + 8 h .. +7.
@@ -275,17 +293,37 @@ __device__ __forceinline__ void compute_step(const unsigned char* st, int k0, in
                                              int N, int jq, int hf, int lane, const bf16x8* qf,
                                              float sc_log2, f32x16* oacc, float& m_i,
                                              float& l_i) {
-  // S^T = K Q^T for the 64 keys (two 32-key tiles).
+  // S^T = K Q^T for the 64 keys (two 32-key tiles): every operand read is
+  // issued before the first product, and the first V^T operands arrive during
+  // the softmax.  Left to the scheduler, each product of the first key tile
+  // waited for a read issued after the one before it (a read's latency is
+  // longer than a product), and so did every second product of O^T.  What
+  // remains is bound by power: the same launch on all-zero inputs runs 34%
+  // faster (as a large matrix product does, 29%), so the earlier operands
+  // shorten dense 16384 x 32 heads by 7% on zeros and by 3.2% on real data
+  // (1993 -> 1931 us, 1.14 PFLOP/s; a large matrix product: 1.36), the sparse
+  // 128k layer, with the cheaper stage copies, by 3% (6210 -> 6032 us).
   f32x16 sacc[2];
+  bf16x8 kf[2][8];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
+  for (int s = 0; s < 8; ++s)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) kf[u][s] = read_k(st, 32 * u + jq, s, hf);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int r = 0; r < 16; ++r) sacc[u][r] = 0.0f;
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
-      sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k(st, 32 * u + jq, s, hf), qf[s],
-                                                       sacc[u], 0, 0, 0);
-  }
+  for (int s = 0; s < 8; ++s)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[u][s], qf[s], sacc[u], 0, 0, 0);
+  __builtin_amdgcn_sched_group_barrier(0x100, 16, 0);   // 16 LDS reads
+  __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);   // 16 MFMAs
+  bf16x8 vf[2][4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) vf[0][s] = read_vt(st, 0, s, lane);
+  asm volatile("" ::: "memory");   // (keeps these reads ahead of the softmax)
   // mask keys after the query (causal) or at / past N; branch-free
   const bool need_mask = (MODE != kDenseFull && k0 + kSub - 1 > qw0) || (k0 + kSub > N);
   if (need_mask) {
@@ -341,13 +379,20 @@ __device__ __forceinline__ void compute_step(const unsigned char* st, int k0, in
     probs((m_i == -INFINITY) ? 0.0f : -m_i);
   }
   l_i += lsum;
-  // O^T += V^T P^T
+  // O^T += V^T P^T, the operands of the next head-dim tile read ahead
 #pragma unroll
-  for (int d = 0; d < 4; ++d)
+  for (int d = 0; d < 4; ++d) {
+    if (d < 3) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) vf[(d + 1) & 1][s] = read_vt(st, d + 1, s, lane);
+    }
 #pragma unroll
     for (int s = 0; s < 4; ++s)
-      oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_vt(st, d, s, lane), as_bf16x8(pw[s]),
-                                                       oacc[d], 0, 0, 0);
+      oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[d & 1][s], as_bf16x8(pw[s]), oacc[d], 0,
+                                                       0, 0);
+    __builtin_amdgcn_sched_group_barrier(0x100, 8, 1);
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 1);
+  }
 }
 
 // O = O^T / l for the lane's query row, bf16.
@@ -405,10 +450,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(
       // (the previous item's closing barrier keeps this write after every
       // wave's read of the last item)
       __syncthreads();
-      const unsigned xs = s_x;
+      // (wave-uniform: everything derived from the item stays in scalar registers)
+      const unsigned xs = __builtin_amdgcn_readfirstlane(s_x);
       if (xs == kXcds) return;   // every queue is empty
       unsigned bg;
-      plan_item(plan, xs, s_idx, n_tiles, G, (unsigned)(B * Hkv), tile, hh, bg);
+      plan_item(plan, xs, __builtin_amdgcn_readfirstlane(s_idx), n_tiles, G, (unsigned)(B * Hkv), tile, hh, bg);
       b = (int)(bg / (unsigned)Hkv);
       g = (int)(bg % (unsigned)Hkv);
     } else if (MODE != kSparse) {
@@ -489,13 +535,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(
     };
 
     // byte offsets of this lane's stage copies inside a 64-row block
-    uint32_t koff[4], voff[4];
-  #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = 16 * wave + 4 * j + (lane >> 4);
-      koff[j] = (uint32_t)(row * kRowBytes + 16 * swz(row, lane & 15));
-      voff[j] = (uint32_t)(row * kRowBytes + 16 * swz_v(row, lane & 15));
-    }
+    uint32_t koff[4], voff;
+    stage_offsets<4>(wave, lane, koff, voff);
 
     f32x16 oacc[4];
   #pragma unroll
@@ -517,14 +558,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(
         compute_step<MODE>(st, k0, qw0, qrow, N, jq, hf, lane, qf, sc_log2, oacc, m_i, l_i);
       if (i + 2 < n_steps) {
         __syncthreads();   // every wave is done reading this stage
-        issue_stage(st, kh, vh, step_key0(i + 2), N, wave, lane, koff, voff);
+        issue_stage<4>(st, kh, vh, step_key0(i + 2), N, wave, lane, koff, voff);
       }
     };
     // Q fragments (and the list) have landed before any stage copy is issued,
     // so no later wait on them covers the copies in flight.
     EI_WAIT_VMCNT(0);
-    if (n_steps > 0) issue_stage(stage0, kh, vh, step_key0(0), N, wave, lane, koff, voff);
-    if (n_steps > 1) issue_stage(stage1, kh, vh, step_key0(1), N, wave, lane, koff, voff);
+    if (n_steps > 0) issue_stage<4>(stage0, kh, vh, step_key0(0), N, wave, lane, koff, voff);
+    if (n_steps > 1) issue_stage<4>(stage1, kh, vh, step_key0(1), N, wave, lane, koff, voff);
     for (int i = 0; i < n_steps; i += 2) {
       step(i, stage0);
       if (i + 1 < n_steps) step(i + 1, stage1);
@@ -606,37 +647,6 @@ hipError_t launch_t(const uint16_t* q, const uint16_t* k, const uint16_t* v, con
 // attn_kernel's bit for bit.
 constexpr int kUnionThreads = 2 * kThreads;
 constexpr int kUnionWords = kUnionMaxBlocks / 32;
-
-// Stage copy by 8 waves: wave w moves rows 8 w .. 8 w + 7 of K and of V.
-__device__ __forceinline__ void issue_stage8(unsigned char* stage, const uint16_t* __restrict__ kh,
-                                             const uint16_t* __restrict__ vh, int k0, int N,
-                                             int wave, int lane, const uint32_t* koff,
-                                             const uint32_t* voff) {
-  const int pos = lane & 15;
-  const uint32_t base = (uint32_t)(uintptr_t)stage;
-  if (k0 + kSub <= N) {
-    const unsigned char* kb = (const unsigned char*)kh + (size_t)k0 * kRowBytes;
-    const unsigned char* vb = (const unsigned char*)vh + (size_t)k0 * kRowBytes;
-    const uint32_t dst0 =
-        base + (uint32_t)(8 * __builtin_amdgcn_readfirstlane(wave) * kRowBytes);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      copy16_to_lds_s(kb, koff[j], dst0 + 4 * j * kRowBytes);
-      copy16_to_lds_s(vb, voff[j], dst0 + 4 * j * kRowBytes + kTileBytes);
-    }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = 8 * wave + 4 * j + (lane >> 4);
-    const int grow = min(k0 + row, N - 1);
-    const size_t roff = (size_t)grow * kHeadDim;
-    const uint32_t dst = base + (uint32_t)((8 * wave + 4 * j) * kRowBytes);
-    copy16_to_lds(kh + roff + 8 * swz(row, pos), __builtin_amdgcn_readfirstlane(dst));
-    copy16_to_lds(vh + roff + 8 * swz_v(row, pos),
-                  __builtin_amdgcn_readfirstlane(dst + kTileBytes));
-  }
-}
 
 template <int SUB>
 __global__ __launch_bounds__(kUnionThreads, 1) void attn_union_kernel(
@@ -737,13 +747,8 @@ __global__ __launch_bounds__(kUnionThreads, 1) void attn_union_kernel(
     return (SUB == 1 ? blk : blk * SUB + (i & 1)) * kSub;
   };
 
-  uint32_t koff[2], voff[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = 8 * wave + 4 * j + (lane >> 4);
-    koff[j] = (uint32_t)(row * kRowBytes + 16 * swz(row, lane & 15));
-    voff[j] = (uint32_t)(row * kRowBytes + 16 * swz_v(row, lane & 15));
-  }
+  uint32_t koff[2], voff;
+  stage_offsets<2>(wave, lane, koff, voff);
 
   f32x16 oacc[4];
 #pragma unroll
@@ -763,12 +768,12 @@ __global__ __launch_bounds__(kUnionThreads, 1) void attn_union_kernel(
       compute_step<kSparse>(st, k0, qw0, qrow, N, jq, hf, lane, qf, sc_log2, oacc, m_i, l_i);
     if (i + 2 < n_steps) {
       __syncthreads();   // every wave is done reading this stage
-      issue_stage8(st, kh, vh, key0(entry(i + 2), i + 2), N, wave, lane, koff, voff);
+      issue_stage<2>(st, kh, vh, key0(entry(i + 2), i + 2), N, wave, lane, koff, voff);
     }
   };
   EI_WAIT_VMCNT(0);
-  if (n_steps > 0) issue_stage8(stage0, kh, vh, key0(entry(0), 0), N, wave, lane, koff, voff);
-  if (n_steps > 1) issue_stage8(stage1, kh, vh, key0(entry(1), 1), N, wave, lane, koff, voff);
+  if (n_steps > 0) issue_stage<2>(stage0, kh, vh, key0(entry(0), 0), N, wave, lane, koff, voff);
+  if (n_steps > 1) issue_stage<2>(stage1, kh, vh, key0(entry(1), 1), N, wave, lane, koff, voff);
   for (int i = 0; i < n_steps; i += 2) {
     step(i, stage0);
     if (i + 1 < n_steps) step(i + 1, stage1);
