@@ -147,8 +147,10 @@ __device__ __forceinline__ void issue_stage(unsigned char* stage, const uint16_t
                                             uint32_t voff) {
   const uint32_t dst = (uint32_t)(uintptr_t)stage +
                        (uint32_t)(4 * NC * __builtin_amdgcn_readfirstlane(wave) * kRowBytes);
-  const unsigned char* kb = (const unsigned char*)kh + (size_t)k0 * kRowBytes;
-  const unsigned char* vb = (const unsigned char*)vh + (size_t)k0 * kRowBytes;
+  // (the second half of a last 128-key block may lie past the sequence's end)
+  const int kc = min(k0, N - 1);
+  const unsigned char* kb = (const unsigned char*)kh + (size_t)kc * kRowBytes;
+  const unsigned char* vb = (const unsigned char*)vh + (size_t)kc * kRowBytes;
   if (k0 + kSub <= N) {   // whole block inside the sequence
     copy_rows_to_lds<NC>(kb, koff, dst);
     uint32_t vo[NC];
@@ -160,7 +162,7 @@ __device__ __forceinline__ void issue_stage(unsigned char* stage, const uint16_t
 #pragma unroll
   for (int j = 0; j < NC; ++j) {   // the block that holds the sequence's end
     const int row = 4 * NC * wave + 4 * j + (lane >> 4), pos = lane & 15;
-    const uint32_t roff = (uint32_t)(min(row, N - 1 - k0) * kRowBytes);
+    const uint32_t roff = (uint32_t)((min(k0 + row, N - 1) - kc) * kRowBytes);
     copy_row_to_lds(kb, roff + 16 * swz(row, pos), dst + 1024 * j);
     copy_row_to_lds(vb, roff + 16 * swz_v(row, pos), dst + 1024 * j + kTileBytes);
   }

@@ -293,6 +293,23 @@ def test_sparse_attention_running_max_jumps():
     assert np.abs(got - ref).max() <= ATTN_ABS
 
 
+@pytest.mark.parametrize("N", [1281, 1300, 1344, 1345, 1407])
+def test_last_128_block_past_the_end(N):
+    """With 128-key blocks and N mod 128 in 1 .. 64, the second 64-key half of
+    the last block lies wholly past the sequence: its copies read the last row
+    instead (in a launch of more than 128 tiles, by the ordinary and the
+    GQA-union kernel), against the oracle."""
+    w = synth.make("c1", 17, Hq=16, Hkv=4, N=N, Ls=256, Lb=128, base_budget=512)
+    r = run_path(w)
+    rows = np.array([[0, h, i] for h in range(w.Hq) for i in range(max(0, N - 150), N)], np.int32)
+    check_attention(w, r, rows)
+    idx, cnt = (torch.from_numpy(r["sel"][n]).cuda() for n in ("idx", "cnt"))
+    ou = eb.sparse_prefill_attn(r["q"], r["k"], r["v"], idx, cnt, w.Ls, w.Lb, w.softmax_scale,
+                                gqa_union=True)
+    torch.cuda.synchronize()
+    assert torch.equal(ou, r["o"])
+
+
 def test_deterministic():
     w = synth.make("c2", 3, N=4096)
     a = run_path(w)
