@@ -38,6 +38,9 @@
 // stealing evens out the groups' different loads.  Without a workspace (or
 // for KV-group counts that do not tile the XCDs) the grid is static: the KV
 // groups rotate over the XCDs every 4 tiles, heaviest tiles first.
+//
+// Launches of few tiles (attn_split_kernel) split each tile's keys over the
+// waves instead, dense and sparse alike.
 #include "ei_internal.h"
 
 #include <math.h>
@@ -206,6 +209,9 @@ __device__ __forceinline__ bf16x8 read_vt(const unsigned char* stage, int dt, in
 #define EI_WAIT_VMCNT(n) \
   __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (15 << 8))
 
+// Wait until every LDS read of this wave has returned (lgkmcnt 0, others max).
+#define EI_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4))
+
 // The persistent sparse schedule (see the file comment).  S = 1: XCD x owns
 // the KV groups x, x + 8, ... (ngx of them), its queue running over chunks of
 // kHeadRun tile ranks (heaviest first) and, inside a chunk, over its (group,
@@ -290,11 +296,16 @@ __device__ __forceinline__ int valid_prefix(const int32_t* lst, int c, int CB, i
 // One 64-key sub-block (staged at st, first key k0) for the wave's 32 query
 // rows: S^T = K Q^T, the causal / length mask, the online softmax with lazy
 // rescaling, and O^T += V^T P^T.
-template <int MODE>
+// `scored` runs once the K operands have been read.  With LATE_V the V tile is
+// read after the softmax only, behind `v_ready`.
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <int MODE, bool LATE_V = false, class Scored = Nothing, class VReady = Nothing>
 __device__ __forceinline__ void compute_step(const unsigned char* st, int k0, int qw0, int qrow,
                                              int N, int jq, int hf, int lane, const bf16x8* qf,
-                                             float sc_log2, f32x16* oacc, float& m_i,
-                                             float& l_i) {
+                                             float sc_log2, f32x16* oacc, float& m_i, float& l_i,
+                                             Scored scored = {}, VReady v_ready = {}) {
   // S^T = K Q^T for the 64 keys (two 32-key tiles): every operand read is
   // issued before the first product, and the first V^T operands arrive during
   // the softmax.  Left to the scheduler, each product of the first key tile
@@ -322,10 +333,13 @@ __device__ __forceinline__ void compute_step(const unsigned char* st, int k0, in
       sacc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[u][s], qf[s], sacc[u], 0, 0, 0);
   __builtin_amdgcn_sched_group_barrier(0x100, 16, 0);   // 16 LDS reads
   __builtin_amdgcn_sched_group_barrier(0x008, 16, 0);   // 16 MFMAs
+  scored();
   bf16x8 vf[2][4];
+  if constexpr (!LATE_V) {
 #pragma unroll
-  for (int s = 0; s < 4; ++s) vf[0][s] = read_vt(st, 0, s, lane);
-  asm volatile("" ::: "memory");   // (keeps these reads ahead of the softmax)
+    for (int s = 0; s < 4; ++s) vf[0][s] = read_vt(st, 0, s, lane);
+    asm volatile("" ::: "memory");   // (keeps these reads ahead of the softmax)
+  }
   // mask keys after the query (causal) or at / past N; branch-free
   const bool need_mask = (MODE != kDenseFull && k0 + kSub - 1 > qw0) || (k0 + kSub > N);
   if (need_mask) {
@@ -382,6 +396,11 @@ __device__ __forceinline__ void compute_step(const unsigned char* st, int k0, in
   }
   l_i += lsum;
   // O^T += V^T P^T, the operands of the next head-dim tile read ahead
+  if constexpr (LATE_V) {
+    v_ready();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) vf[0][s] = read_vt(st, 0, s, lane);
+  }
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
     if (d < 3) {
@@ -579,6 +598,205 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(
   }
 }
 
+// ---------------------------------------------------------------------------
+// Small launches.  A launch of few tiles leaves most CUs idle while each of
+// its waves walks its tile's keys in turn (a 1024-token, 4-head layer: 32
+// workgroups of up to 16 steps of ~1 us).  Here a workgroup takes a 32-row tile
+// and its four waves every fourth step of the tile's keys, each with a stage
+// of its own in LDS (no barrier inside the loop: a wave waits for its own
+// copies only, the next step's K copied once this step's scores have been
+// read, its V after the last product); the four partial (m, l, O) are merged
+// through LDS at the end.  The same rows, blocks and arithmetic per step as
+// attn_kernel, so the result differs only by the order of the sums.
+constexpr int kSplitWaves = kThreads / kWave;
+constexpr int kSplitTileQ = 32;
+
+// The wave's own 64-row K (or V) tile: four groups of four 1 KB copies.
+__device__ __forceinline__ void issue_tile(unsigned char* dst, const uint16_t* __restrict__ src,
+                                           int k0, int N, int lane, const uint32_t* off,
+                                           bool is_v) {
+  const int kc = min(k0, N - 1);   // (as in issue_stage)
+  const unsigned char* sb = (const unsigned char*)src + (size_t)kc * kRowBytes;
+  const uint32_t d0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
+  if (k0 + kSub <= N) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) copy_rows_to_lds<4>(sb + 4096 * g, off, d0 + 4096 * g);
+    return;
+  }
+  // (opaque: the 16 row offsets are formed here, not kept across the loop)
+  asm volatile("" : "+v"(lane));
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const int row = 4 * j + (lane >> 4), pos = lane & 15;
+    copy_row_to_lds(sb, (uint32_t)((min(k0 + row, N - 1) - kc) * kRowBytes) +
+                            16 * (is_v ? swz_v(row, pos) : swz(row, pos)),
+                    d0 + 1024 * j);
+  }
+}
+
+template <int MODE, int SUB>
+__global__ __launch_bounds__(kThreads, 1) void attn_split_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+    const uint16_t* __restrict__ v, uint16_t* __restrict__ o, int Hq, int Hkv, int N, int n_tiles,
+    int Ls, int CS, int CB, float sc_log2, const int32_t* __restrict__ bidx,
+    const int32_t* __restrict__ bcnt, int kmax) {
+  __shared__ __attribute__((aligned(1024))) unsigned char stages[kSplitWaves][kStageBytes];
+  __shared__ float part_m[kSplitWaves][kSplitTileQ], part_l[kSplitWaves][kSplitTileQ];
+  const int rows = gridDim.x / n_tiles;   // (batch, query head) pairs
+  const int tile = n_tiles - 1 - (int)blockIdx.x / rows, bh = (int)blockIdx.x % rows;
+  const int b = bh / Hq, h = bh % Hq, g = h / (Hq / Hkv);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int jq = lane & 31, hf = lane >> 5;
+  const int q0 = tile * kSplitTileQ, q_last = min(q0 + kSplitTileQ - 1, N - 1), qrow = q0 + jq;
+  const uint16_t* kh = k + (size_t)(b * Hkv + g) * N * kHeadDim;
+  const uint16_t* vh = v + (size_t)(b * Hkv + g) * N * kHeadDim;
+
+  bf16x8 qf[8];
+  {
+    const uint16_t* qp = q + ((size_t)bh * N + qrow) * kHeadDim + 8 * hf;
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      qf[s] = as_bf16x8(qrow < N ? *(const uint4*)(qp + 16 * s) : make_uint4(0, 0, 0, 0));
+  }
+  const int32_t* lst = nullptr;
+  int n_steps;
+  if (MODE == kSparse) {
+    const int64_t row = (int64_t)bh * CS + q0 / Ls;
+    lst = bidx + row * kmax;
+    n_steps = valid_prefix<SUB>(lst, min(max(bcnt[row], 0), kmax), CB, q_last, lane) * SUB;
+  } else {
+    n_steps = MODE == kDenseCausal ? q_last / kSub + 1 : (N + kSub - 1) / kSub;
+  }
+  // lane t: the list entry of the wave's t-th step (read here once: a load in
+  // the loop would be waited for behind the copies)
+  int lv = 0;
+  if (MODE == kSparse) {
+    const int e = (wave + kSplitWaves * lane) / SUB;
+    if (e < n_steps / SUB) lv = lst[e];
+    asm volatile("" : "+v"(lv));
+  }
+  auto step_key0 = [&](int i) -> int {
+    if (MODE != kSparse) return i * kSub;
+    const int blk = __builtin_amdgcn_readlane(lv, (i / kSplitWaves) & (kWave - 1));
+    return (SUB == 1 ? blk : blk * SUB + (i & 1)) * kSub;
+  };
+  unsigned char* st = stages[wave];
+  uint32_t koff[4], voff[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    koff[j] = (uint32_t)((lane >> 4) * kRowBytes + 16 * swz(4 * j + (lane >> 4), lane & 15));
+    voff[j] = (uint32_t)((lane >> 4) * kRowBytes + 16 * swz_v(lane >> 4, lane & 15));
+  }
+
+  f32x16 oacc[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[d][r] = 0.0f;
+  float m_i = -INFINITY, l_i = 0.0f;
+
+  EI_WAIT_VMCNT(0);   // the Q operands: no later wait covers copies in flight
+  int k0 = 0;
+  if (wave < n_steps) {
+    k0 = step_key0(wave);
+    issue_tile(st, kh, k0, N, lane, koff, false);
+    issue_tile(st + kTileBytes, vh, k0, N, lane, voff, true);
+  }
+  for (int i = wave; i < n_steps; i += kSplitWaves) {
+    const bool more = i + kSplitWaves < n_steps;
+    const int kn = more ? step_key0(i + kSplitWaves) : 0;
+    EI_WAIT_VMCNT(16);   // K has landed (V's 16 copies may be in flight)
+    asm volatile("" ::: "memory");
+    // (every LDS read of a tile has returned before its copies are issued)
+    auto next_k = [&]() {
+      EI_WAIT_LGKM0();
+      if (more) issue_tile(st, kh, kn, N, lane, koff, false);
+    };
+    auto wait_v = [&]() {
+      if (more) EI_WAIT_VMCNT(16); else EI_WAIT_VMCNT(0);
+      asm volatile("" ::: "memory");
+    };
+    if (MODE == kDenseFull || k0 <= q_last) {
+      compute_step<MODE, true>(st, k0, q0, qrow, N, jq, hf, lane, qf, sc_log2, oacc, m_i, l_i,
+                               next_k, wait_v);
+    } else {
+      next_k();
+      wait_v();
+    }
+    EI_WAIT_LGKM0();
+    if (more) issue_tile(st + kTileBytes, vh, kn, N, lane, voff, true);
+    k0 = kn;
+  }
+
+  // Merge: each wave leaves its O in its own stage (every read and copy of
+  // which is done), then takes 32 of the 128 dims of all four.
+  const float l = l_i + __shfl_xor(l_i, 32);
+  if (hf == 0) {
+    part_m[wave][jq] = m_i;
+    part_l[wave][jq] = l;
+  }
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      *(float4*)(st + ((d * 4 + r) * kWave + lane) * 16) =
+          make_float4(oacc[d][4 * r], oacc[d][4 * r + 1], oacc[d][4 * r + 2], oacc[d][4 * r + 3]);
+  __syncthreads();
+  float m = part_m[0][jq];
+#pragma unroll
+  for (int w = 1; w < kSplitWaves; ++w) m = fmaxf(m, part_m[w][jq]);
+  float f[kSplitWaves], lsum = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kSplitWaves; ++w) {
+    const float mw = part_m[w][jq];
+    f[w] = mw == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mw - m);
+    lsum += f[w] * part_l[w][jq];
+  }
+  const float inv = lsum > 0.0f ? 1.0f / lsum : 0.0f;
+  if (qrow >= N) return;
+  uint16_t* op = o + ((size_t)bh * N + qrow) * kHeadDim + 32 * wave + 4 * hf;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; ++w) {
+      const float4 x = *(const float4*)(stages[w] + ((wave * 4 + r) * kWave + lane) * 16);
+      a.x += f[w] * x.x;
+      a.y += f[w] * x.y;
+      a.z += f[w] * x.z;
+      a.w += f[w] * x.w;
+    }
+    *(uint2*)(op + 8 * r) =
+        make_uint2(pack_bf16x2(a.x * inv, a.y * inv), pack_bf16x2(a.z * inv, a.w * inv));
+  }
+}
+
+// The split takes a launch of at most kSplitMaxTiles 128-row tiles (half the
+// CUs).  Its 32-row tiles are four times as many, one to a CU (128 KB of LDS),
+// and each copies its keys for itself, so it stops paying once the 128-row
+// tiles fill the chip.  128-row against 32-row split tiles: 4 heads, 1024
+// tokens (32 tiles) 24.8 / 15.4 us, 2048 (64) 44.3 / 19.2, 4096 (128) 82.9 /
+// 38.3; dense, 4 heads, 4096 tokens (128) causal 80.3 / 35.8, full 80.8 / 51.1;
+// 16 heads, 900 tokens (128) 21.5 / 16.9; but 32 heads, 896 tokens (224) 22.0 /
+// 28.8.  (At 128 tiles a wave has at most 64 steps, one list entry per lane.)
+constexpr int kSplitMaxTiles = 128;
+static_assert(kSplitMaxTiles * kTileQ / kSub <= kSplitWaves * kWave, "a lane per step of a wave");
+bool split_tiles(const AttnShape& s) {
+  return (int64_t)s.B * s.Hq * ((s.N + kTileQ - 1) / kTileQ) <= kSplitMaxTiles;
+}
+
+template <int MODE, int SUB>
+hipError_t launch_split_t(const uint16_t* q, const uint16_t* k, const uint16_t* v,
+                          const AttnShape& s, const int32_t* bidx, const int32_t* bcnt,
+                          uint16_t* o, hipStream_t stream) {
+  const int n_tiles = (s.N + kSplitTileQ - 1) / kSplitTileQ;
+  const float sc_log2 = (float)((double)s.softmax_scale * 1.4426950408889634);
+  hipLaunchKernelGGL((attn_split_kernel<MODE, SUB>), dim3((unsigned)(s.B * s.Hq * n_tiles)),
+                     dim3(kThreads), 0, stream, q, k, v, o, s.Hq, s.Hkv, s.N, n_tiles, s.Ls, s.CS,
+                     s.CB, sc_log2, bidx, bcnt, s.kmax);
+  return hipGetLastError();
+}
+
 // The persistent plan for a shape, if its KV groups tile the XCDs.
 bool make_plan(const AttnShape& s, int n_tiles, XcdPlan& pl) {
   const unsigned NG = (unsigned)(s.B * s.Hkv), G = (unsigned)(s.Hq / s.Hkv);
@@ -614,6 +832,7 @@ template <int MODE, int SUB>
 hipError_t launch_t(const uint16_t* q, const uint16_t* k, const uint16_t* v, const AttnShape& s,
                     const int32_t* bidx, const int32_t* bcnt, uint16_t* o, uint32_t* sched,
                     bool sched_zeroed, hipStream_t stream) {
+  if (split_tiles(s)) return launch_split_t<MODE, SUB>(q, k, v, s, bidx, bcnt, o, stream);
   const int n_tiles = (s.N + kTileQ - 1) / kTileQ;
   const int64_t total = (int64_t)s.B * s.Hq * n_tiles;
   int64_t grid = (total + kXcds - 1) / kXcds * kXcds;
@@ -789,6 +1008,8 @@ template <int SUB>
 hipError_t launch_union_t(const uint16_t* q, const uint16_t* k, const uint16_t* v,
                           const AttnShape& s, const int32_t* bidx, const int32_t* bcnt,
                           uint16_t* o, hipStream_t stream) {
+  // (bitwise the per-head kernel's output, so also the same kernel here)
+  if (split_tiles(s)) return launch_split_t<kSparse, SUB>(q, k, v, s, bidx, bcnt, o, stream);
   const int n_tiles = (s.N + kTileQ - 1) / kTileQ;
   const int npair = (s.Hq / s.Hkv + 1) / 2;
   const int64_t grid = (int64_t)s.B * s.Hkv * npair * n_tiles;

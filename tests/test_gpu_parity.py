@@ -310,6 +310,61 @@ def test_last_128_block_past_the_end(N):
     assert torch.equal(ou, r["o"])
 
 
+@pytest.mark.parametrize("N", [1, 31, 33, 64, 97, 129, 1000, 2048, 4096])
+@pytest.mark.parametrize("tiling", [(128, 64), (256, 128)])
+def test_split_tiles_equal_large_launch(N, tiling):
+    """A launch of at most 128 tiles takes the kernel whose waves share a
+    tile's keys out and merge their sums; five batch entries of the same heads
+    (or one more head at 4096 tokens) take the ordinary one.  Dense causal,
+    dense full and sparse (lists without the first block, gaps, an empty list)
+    agree to bf16 rounding, and with the oracle."""
+    Hq, Hkv = 4, 2
+    w = synth.make("c1", 31, Hq=Hq, Hkv=Hkv, N=N)
+    q, k, v = to_dev(w.q), to_dev(w.k), to_dev(w.v)
+    Ls, Lb = tiling
+    CS, CB, r = -(-N // Ls), -(-N // Lb), Ls // Lb
+    km = CB
+    idx = np.full((1, Hq, CS, km), -1, np.int32)
+    cnt = np.zeros((1, Hq, CS), np.int32)
+    rng = np.random.default_rng(N)
+    for h in range(Hq):
+        for s in range(CS):
+            past = np.flatnonzero(rng.random(s * r) < (0.9, 0.3, 1.0, 0.0)[h])
+            blk = np.concatenate([past, np.arange(s * r, min((s + 1) * r, CB))])
+            if h == 3 and s % 3 == 1:
+                blk = blk[:0]                       # no key at all: zero rows
+            idx[0, h, s, :len(blk)] = blk
+            cnt[0, h, s] = len(blk)
+    reps = 5 if N < 4096 else 2
+    big = lambda t: t.repeat(reps, *([1] * (t.dim() - 1))).contiguous()
+    idx_t, cnt_t = torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda()
+    rows = np.array([[0, h, i] for h in range(Hq) for i in range(0, N, 1 if N < 1200 else 7)],
+                    np.int32)
+    for mode in ("causal", "full", "sparse"):
+        def run(q, k, v, idx, cnt):
+            if mode == "sparse":
+                return eb.sparse_prefill_attn(q, k, v, idx, cnt, Ls, Lb, w.softmax_scale)
+            return eb.dense_prefill_attn(q, k, v, w.softmax_scale, mode == "causal")
+        o = run(q, k, v, idx_t, cnt_t)
+        ob = run(*(big(t) for t in (q, k, v, idx_t, cnt_t)))
+        torch.cuda.synchronize()
+        small, large = o[0].float(), ob[0].float()
+        # Both round each probability to bf16 (2^-9 of it) against a running
+        # maximum of their own, so each output, a mean of v weighted by the
+        # probabilities, moves by at most 2^-9 max |v| in either; their own
+        # rounding to bf16 is half a step (2^-8) in either.
+        bound = 2 * (2.0 ** -8 * large.abs() + 2.0 ** -9 * float(v.float().abs().max()))
+        assert bool(((small - large).abs() <= 1.01 * bound).all()), mode
+        args = (idx, cnt, Ls, Lb) if mode == "sparse" else ()
+        ref = oracle.attention(w.q, w.k, w.v, rows, w.softmax_scale, mode != "full", *args)
+        if mode == "sparse":   # no key: 0 / 0 in the oracle, a zero row here
+            empty = cnt[0, rows[:, 1], rows[:, 2] // Ls] == 0
+            assert np.isnan(ref[empty]).all()
+            ref[empty] = 0.0
+        err = np.abs(bf16_to_f64(o)[rows[:, 0], rows[:, 1], rows[:, 2]] - ref)
+        assert err.max() <= ATTN_ABS, (mode, err.max())
+
+
 def test_deterministic():
     w = synth.make("c2", 3, N=4096)
     a = run_path(w)
