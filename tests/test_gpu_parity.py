@@ -452,6 +452,20 @@ def test_persistent_schedule_equals_static(wl, seed, case):
         assert torch.equal(o, o_static), f"call {call}"
 
 
+@pytest.mark.parametrize("wl,seed,case", [
+    ("c1", 4, dict(B=4, Hq=16, Hkv=4, N=2048)),              # 16 groups, 1024 items
+    ("c1", 4, dict(B=2, Hq=16, Hkv=2, N=3072 + 65)),         # four groups, 800 items
+    ("c1", 4, dict(Hq=8, Hkv=1, N=9000)),                    # one group, 568 items
+    ("c1", 7, dict(B=2, Hq=16, Hkv=4, N=4096 - 90, Ls=256, Lb=128)),   # 1024 items
+    ("c1", 7, dict(B=2, Hq=16, Hkv=4, N=2304, base_budget=1024)),   # longer items
+], ids=lambda x: x if isinstance(x, str) else None)
+def test_persistent_queues(wl, seed, case):
+    """The persistent schedule proper (more items than it has workgroups),
+    with items short enough to draw the next ticket while they run and with
+    longer ones: bitwise the static grid's output, twice."""
+    test_persistent_schedule_equals_static(wl, seed, case)
+
+
 def test_binding_refuses_mismatched_tensors():
     """k / v / score tensors that do not match q's sizes raise before any launch."""
     w = synth.make("c1", 4, N=512)
