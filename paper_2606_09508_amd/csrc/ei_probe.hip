@@ -243,8 +243,8 @@ __device__ __forceinline__ void fold_rows(const uint4 (&w)[BL], float (&mx)[8], 
   }
 }
 
-// Four whole query segments (items it[0..3], each L_S = 128 rows, so 32 rows
-// a lane) pooled by one wave as one stream of batches of BL loads a lane, NB
+// Four whole query segments (head, seg; each L_S = 128 rows, so 32 rows a
+// lane) pooled by one wave as one stream of batches of BL loads a lane, NB
 // batches in flight (a batch's slot is refilled as soon as it is folded), so
 // the stream runs on across segment boundaries; a segment is split and
 // written as soon as its last batch is folded.  The segment bases are
@@ -252,7 +252,7 @@ __device__ __forceinline__ void fold_rows(const uint4 (&w)[BL], float (&mx)[8], 
 // round trips of 16 loads each): 1-3% faster probe, same records.
 constexpr int kQBatch = 4, kQRing = 4;
 __device__ __forceinline__ void pool_query4(const uint16_t* __restrict__ q, int N,
-                                            const int64_t (&it)[4], int CS,
+                                            const int64_t (&head)[4], const int (&seg)[4], int CS,
                                             unsigned char* __restrict__ ws, const Layout& lay,
                                             int lane) {
   constexpr int BL = kQBatch, NB = kQRing, PER = 32 / BL, NBAT = 4 * PER;
@@ -261,8 +261,8 @@ __device__ __forceinline__ void pool_query4(const uint16_t* __restrict__ q, int 
   const unsigned char* base[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t)
-    base[t] = (const unsigned char*)(q + ((size_t)(it[t] / CS) * N + (size_t)(it[t] % CS) * 128) *
-                                             kHeadDim);
+    base[t] =
+        (const unsigned char*)(q + ((size_t)head[t] * N + (size_t)seg[t] * 128) * kHeadDim);
   uint4 w[NB][BL];
   auto issue = [&](int b) {
 #pragma unroll
@@ -289,37 +289,33 @@ __device__ __forceinline__ void pool_query4(const uint16_t* __restrict__ q, int 
         mn[e] = fminf(mn[e], __shfl_xor(mn[e], 16));
         mn[e] = fminf(mn[e], __shfl_xor(mn[e], 32));
       }
-      if (ph < 2) store_query(ph == 0 ? mx : mn, it[b / PER], ws, lay, lane);
+      if (ph < 2)
+        store_query(ph == 0 ? mx : mn, head[b / PER] * CS + seg[b / PER], ws, lay, lane);
     }
   }
 }
 
-// One wave per item: a query segment (B*Hq*C_S items) or a key block slot
-// (B*Hkv*C_Bt*16 items, C_Bt = ceil(C_B / 16); slots past C_B are written as
-// zeros).  Lanes c = lane % 16 hold dims 8c .. 8c+7 of rows of phase
-// lane / 16; after the reduction lanes 0-15 split the max vector and lanes
-// 16-31 the min vector.
-__device__ __forceinline__ void pool_item(const uint16_t* __restrict__ q,
-                                          const uint16_t* __restrict__ k, int B, int Hq, int Hkv,
-                                          int N, int Ls, int Lb, int CS, int CB, int CBt,
-                                          double sgn, unsigned char* __restrict__ ws,
-                                          const Layout& lay, int64_t item, int lane) {
-  const int64_t nq = (int64_t)B * Hq * CS;
-  const bool is_q = item < nq;
-  const int64_t head = is_q ? item / CS : (item - nq) / ((int64_t)CBt * kTileBlocks);
-  const int grp = (int)(is_q ? item % CS : (item - nq) % ((int64_t)CBt * kTileBlocks));
+// One wave pools query segment grp of query head `head` (IS_Q), or key block
+// slot grp of KV head `head` (C_Bt * 16 slots, C_Bt = ceil(C_B / 16); slots
+// past C_B are written as zeros).  Lanes c = lane % 16 hold dims 8c .. 8c+7 of
+// rows of phase lane / 16; after the reduction lanes 0-15 split the max vector
+// and lanes 16-31 the min vector.
+template <bool IS_Q>
+__device__ __forceinline__ void pool_item(const uint16_t* __restrict__ src, int N, int L, int CS,
+                                          int CB, int CBt, double sgn,
+                                          unsigned char* __restrict__ ws, const Layout& lay,
+                                          int64_t head, int grp, int lane) {
   const int c = lane & 15;   // 16-byte chunk: dims 8c .. 8c+7
   const int ph = lane >> 4;  // row phase 0..3
 
   float mx[8], mn[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) { mx[e] = -INFINITY; mn[e] = INFINITY; }
-  const bool pad = !is_q && grp >= CB;
+  const bool pad = !IS_Q && grp >= CB;
   if (!pad) {
-    const int L = is_q ? Ls : Lb;
     const int64_t row0 = (int64_t)grp * L;
     const int rows = (int)min((int64_t)L, (int64_t)N - row0);
-    const uint16_t* base = (is_q ? q : k) + ((size_t)head * N + row0) * kHeadDim;
+    const uint16_t* base = src + ((size_t)head * N + row0) * kHeadDim;
     int r = ph;
     // 64 rows (16 loads of 16 bytes per lane) in flight at a time: a query
     // segment of 128 rows takes two round trips to HBM, a key block one
@@ -352,8 +348,8 @@ __device__ __forceinline__ void pool_item(const uint16_t* __restrict__ q,
     for (int e = 0; e < 8; ++e) { mx[e] = 0.0f; mn[e] = 0.0f; }
   }
   if (ph >= 2) return;
-  if (is_q) {
-    store_query(ph == 0 ? mx : mn, item, ws, lay, lane);
+  if constexpr (IS_Q) {
+    store_query(ph == 0 ? mx : mn, head * CS + grp, ws, lay, lane);
     return;
   }
   const int m = ph;   // 0: max vector, 1: min vector
@@ -401,10 +397,23 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
     Layout lay, int64_t item_offset, uint32_t* __restrict__ sched) {
   if (sched != nullptr && blockIdx.x == 0 && threadIdx.x < kSchedCounters) sched[threadIdx.x] = 0u;
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t item = item_offset + (int64_t)blockIdx.x * kPoolWaves + (threadIdx.x >> 6);
+  const int64_t item = item_offset + (int64_t)blockIdx.x * kPoolWaves +
+                       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t nq = (int64_t)B * Hq * CS, nk = (int64_t)B * Hkv * CBt * kTileBlocks;
   if (item >= nq + nk) return;
-  pool_item(q, k, B, Hq, Hkv, N, Ls, Lb, CS, CB, CBt, sgn, ws, lay, item, lane);
+  // 32-bit divisions: segments and key tiles number under 2^31 (64-bit ones,
+  // here and in the scores kernel's prologue: probe 0-2% slower)
+  if (item < nq) {
+    const uint32_t head = (uint32_t)item / (uint32_t)CS;
+    pool_item<true>(q, N, Ls, CS, CB, CBt, sgn, ws, lay, head,
+                    (int)((uint32_t)item - head * (uint32_t)CS), lane);
+  } else {
+    const uint32_t tile = (uint32_t)((item - nq) / kTileBlocks), head = tile / (uint32_t)CBt;
+    pool_item<false>(k, N, Lb, CS, CB, CBt, sgn, ws, lay, head,
+                     (int)((tile - head * (uint32_t)CBt) * kTileBlocks) +
+                         (int)((item - nq) % kTileBlocks),
+                     lane);
+  }
 }
 
 
@@ -461,7 +470,7 @@ __device__ __forceinline__ double limb_logit(const i32x4 (&acc)[2][2], int a, in
 
 template <int MODE, int TPS, int SLOTS, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void scores_kernel(
-    const uint16_t* __restrict__ qsrc, int B, int N, int Ls, int Lb,
+    const uint16_t* __restrict__ qsrc, int N, int Ls,
     unsigned char* __restrict__ ws, Layout lay, float* __restrict__ log_scores,
     float* __restrict__ entropy, int Hq, int Hkv, int CS, int CB, int CBt, int r, int n_groups,
     int n_chunks, double ps_abs, double sgn, float tau, UnitStats* __restrict__ ustats,
@@ -477,11 +486,11 @@ __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void 
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
   const int gq = lane >> 4, col = lane & 15;
-  const int wg = blockIdx.x;
-  const int chunk = n_chunks - 1 - wg / n_groups;   // heavier chunks first
-  const int gi = wg % n_groups;                      // (batch, KV head)
-  const int b = gi / Hkv, g = gi % Hkv;
-  const int G = Hq / Hkv;
+  const uint32_t wgc = blockIdx.x / (uint32_t)n_groups;
+  const int chunk = n_chunks - 1 - (int)wgc;                      // heavier chunks first
+  const int gi = (int)(blockIdx.x - wgc * (uint32_t)n_groups);    // (batch, KV head)
+  const int b = (int)((uint32_t)gi / (uint32_t)Hkv), g = gi - b * Hkv;
+  const int G = (int)((uint32_t)Hq / (uint32_t)Hkv);
   const int U = G * CS;
   const int u0 = chunk * kUnits;
   const int ulast = min(u0 + kUnits - 1, U - 1);
@@ -498,9 +507,10 @@ __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void 
   const unsigned char* kmeta = ws + lay.kmeta + (size_t)gi * CBt * kKMetaTile;
   const unsigned char* kcorr = ws + lay.kcorr + (size_t)gi * CBt * kKCorrTile;
 
+  auto unit_seg = [&](int u) -> int { return (int)((uint32_t)u / (uint32_t)G); };
+  auto unit_head = [&](int u) -> int64_t { return b * Hq + g * G + (u - unit_seg(u) * G); };
   auto unit_row = [&](int u) -> int64_t {   // (b, h, s) row of unit u
-    const int s = u / G, hh = u % G;
-    return ((int64_t)(b * Hq + g * G + hh)) * CS + s;
+    return unit_head(u) * CS + unit_seg(u);
   };
 
   // The query segments of the workgroup's own units are pooled here (only
@@ -512,14 +522,15 @@ __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void 
     const int uw = u0 + 4 * KT * __builtin_amdgcn_readfirstlane(wave);
     // whole segments: L_S = 128 and the wave's last unit's segment ends by N
     if (KT == 1 && Ls == 128 && uw + 3 < U && (int64_t)((uw + 3) / G + 1) * 128 <= N) {
-      const int64_t it[4] = {unit_row(uw), unit_row(uw + 1), unit_row(uw + 2), unit_row(uw + 3)};
-      pool_query4(qsrc, N, it, CS, ws, lay, lane);
+      const int64_t head[4] = {unit_head(uw), unit_head(uw + 1), unit_head(uw + 2),
+                               unit_head(uw + 3)};
+      const int seg[4] = {unit_seg(uw), unit_seg(uw + 1), unit_seg(uw + 2), unit_seg(uw + 3)};
+      pool_query4(qsrc, N, head, seg, CS, ws, lay, lane);
     } else {
       for (int t = 0; t < 4 * KT; ++t) {
         const int u = uw + t;
         if (u < U)
-          pool_item(qsrc, nullptr, B, Hq, Hkv, N, Ls, Lb, CS, CB, CBt, sgn, ws, lay, unit_row(u),
-                    lane);
+          pool_item<true>(qsrc, N, Ls, CS, CB, CBt, sgn, ws, lay, unit_head(u), unit_seg(u), lane);
       }
     }
     __syncthreads();
@@ -804,7 +815,7 @@ __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void 
   // the units' LDS rows)
   int np[KT];   // past blocks s r of the lane's unit (0 for a missing unit)
 #pragma unroll
-  for (int kt = 0; kt < KT; ++kt) np[kt] = nv[kt] > 0 ? (int)(urow[kt] % CS) * r : 0;
+  for (int kt = 0; kt < KT; ++kt) np[kt] = nv[kt] > 0 ? unit_seg(u0 + 4 * KT * wave + 4 * kt + gq) * r : 0;
   float H2[KT];
 #pragma unroll
   for (int kt = 0; kt < KT; ++kt) H2[kt] = 0.0f;
@@ -929,7 +940,7 @@ hipError_t launch_fused_select(const ProbeShape& s, const Layout& lay, unsigned 
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)n_groups * n_chunks)),
-                     dim3(kWaves * kWave), lds, stream, nullptr, s.B, s.N, s.Ls, s.Lb, ws, lay, nullptr, nullptr, s.Hq, s.Hkv,
+                     dim3(kWaves * kWave), lds, stream, nullptr, s.N, s.Ls, ws, lay, nullptr, nullptr, s.Hq, s.Hkv,
                      s.CS, s.CB, CBt, s.r,
                      n_groups, n_chunks, ps_abs, sgn, tau, (UnitStats*)(ws + lay.stats), kblocks,
                      idx, cnt, kmax, fused_row_cap(s));
@@ -970,7 +981,7 @@ hipError_t launch_pool_scores(const uint16_t* q, const uint16_t* k, const ProbeS
   auto launch = [&](auto kern, int waves) {
     const int n_chunks = (int)((U + 4 * KT * waves - 1) / (4 * KT * waves));
     hipLaunchKernelGGL(kern, dim3((unsigned)(n_groups * n_chunks)), dim3(waves * kWave), 0, stream,
-                       q, s.B, s.N, s.Ls, s.Lb, ws, lay, log_scores, entropy, s.Hq, s.Hkv, s.CS,
+                       q, s.N, s.Ls, ws, lay, log_scores, entropy, s.Hq, s.Hkv, s.CS,
                        s.CB, CBt, s.r, (int)n_groups, n_chunks, ps_abs, sgn, tau,
                        MODE == kScoresEntropy ? (UnitStats*)(ws + lay.stats) : nullptr, nullptr,
                        nullptr, nullptr, 0, 0);
