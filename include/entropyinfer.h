@@ -400,6 +400,13 @@ ei_status ei_rope_heads(const uint16_t* q_in, const uint16_t* k_in, const uint16
                         uint16_t* q_out, uint16_t* k_out, uint16_t* v_out, void* stream);
 
 /*
+ * ei_rope_tables: cos_table[n][i] and sin_table[n][i] (fp32 [N][ceil(D/2)]) of
+ * the angle n * theta^(-2i / D), theta > 0.
+ */
+ei_status ei_rope_tables(int32_t seq_len, int32_t head_dim, float theta, float* cos_table,
+                         float* sin_table, void* stream);
+
+/*
  * ei_swiglu: out[i] = bf16(silu(g[i])) * u[i] for n elements (a multiple of 8,
  * else EI_ERR_UNSUPPORTED); out may be g or u.
  */

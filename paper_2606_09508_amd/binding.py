@@ -111,6 +111,8 @@ def lib() -> ctypes.CDLL:
                                      _VP, _VP, _VP]
         L.ei_rope_heads.restype = ctypes.c_int
         L.ei_rope_heads.argtypes = [_VP, _VP, _VP, _VP, _VP, Dims, _VP, _VP, _VP, _VP]
+        L.ei_rope_tables.restype = ctypes.c_int
+        L.ei_rope_tables.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_float, _VP, _VP, _VP]
         L.ei_swiglu.restype = ctypes.c_int
         L.ei_swiglu.argtypes = [_VP, _VP, ctypes.c_int64, _VP, _VP]
         _LIB = L
@@ -501,6 +503,19 @@ def rope_heads(q, k, v, cos, sin):
                                  Dims(B, Hq, Hkv, N, D), *(_ptr(t) for t in out), _stream(q))
     _check("ei_rope_heads", st)
     return out
+
+
+def rope_tables(cos, sin, head_dim: int, theta: float) -> None:
+    """ei_rope_tables: fills cos and sin [N, ceil(head_dim / 2)] (fp32)."""
+    for t, n in ((cos, "cos"), (sin, "sin")):
+        _req(t, n, torch.float32, 2)
+        if t.shape != cos.shape or t.shape[1] != (head_dim + 1) // 2:
+            raise ValueError(f"{n} {tuple(t.shape)} is not [N, {(head_dim + 1) // 2}]")
+    _same_device(cos, sin)
+    with _on(cos):
+        st = lib().ei_rope_tables(cos.shape[0], head_dim, float(theta), _ptr(cos), _ptr(sin),
+                                  _stream(cos))
+    _check("ei_rope_tables", st)
 
 
 def swiglu(g, u, out=None):

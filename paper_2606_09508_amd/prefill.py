@@ -83,6 +83,13 @@ def make_weights(shape: DecoderShape, n_layers: int, seed: int, device) -> list[
 
 def rope_tables(N: int, D: int, theta: float, device):
     """cos / sin [N, D/2] (fp32) of the rotary embedding, half-split layout."""
+    if type(N) is int and type(D) is int and type(theta) in (int, float) and N > 0 and D > 0 \
+            and theta > 0 and torch.device(device).type == "cuda":
+        cos, sin = (torch.empty((N, (D + 1) // 2), dtype=torch.float32, device=device)
+                    for _ in range(2))
+        if _plain(cos, sin):
+            eb.rope_tables(cos, sin, D, theta)
+            return cos, sin
     inv = 1.0 / (theta ** (torch.arange(0, D, 2, device=device, dtype=torch.float32) / D))
     ang = torch.arange(N, device=device, dtype=torch.float32)[:, None] * inv[None, :]
     return torch.cos(ang), torch.sin(ang)

@@ -40,6 +40,17 @@ def test_add_rmsnorm(rows, cols):
         _close(h, d * torch.rsqrt((d * d).mean(-1, keepdim=True) + 1e-5) * g.double())
 
 
+@pytest.mark.parametrize("N,D,theta", [(1, 128, 500000.0), (3, 2, 10000.0), (1000, 128, 500000),
+                                       (131072, 128, 500000.0), (257, 96, 1e4)])
+def test_rope_tables(N, D, theta):
+    """The one-launch tables against the tensor operations on the same device:
+    the same fp32 functions in the same order, so bitwise equal."""
+    cos, sin = pf.rope_tables(N, D, theta, torch.device("cuda:0"))
+    inv = 1.0 / (theta ** (torch.arange(0, D, 2, device="cuda", dtype=torch.float32) / D))
+    ang = torch.arange(N, device="cuda", dtype=torch.float32)[:, None] * inv[None, :]
+    assert torch.equal(cos, torch.cos(ang)) and torch.equal(sin, torch.sin(ang))
+
+
 @pytest.mark.parametrize("B,N,Hq,Hkv", [(1, 1, 1, 1), (1, 33, 4, 2), (2, 31, 7, 1), (1, 64, 32, 8),
                                         (3, 100, 5, 5)])
 def test_rope_heads(B, N, Hq, Hkv):
