@@ -478,6 +478,14 @@ __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void 
     int kmax, int row_cap) {
   constexpr int kTilesPerStep = TPS;
   constexpr int kThreads = WAVES * kWave, kUnits = WAVES * 4 * KT;
+  // 32-dim chunks, and key vectors, of the residual's operands loaded together
+  // (a branch per chunk, as the halves were first told apart, waited for each
+  // chunk's loads in turn).  One-wave workgroups have registers for a whole
+  // half (4 heads, 16384 tokens, spread keys 73.5 -> 49.8 us); at the 128 that
+  // keep four four-wave workgroups on a CU more than two chunks of one vector
+  // spill (28 heads, 65536 tokens: 317 -> 304 us, lognormal keys with
+  // retrieval spans 501 -> 422).
+  constexpr int kResBatch = WAVES == kSmallWaves ? 4 : 2, kResVecs = WAVES == kSmallWaves ? 2 : 1;
   // one-wave workgroups find their query segments pooled by pool_kernel
   constexpr bool kPoolsQ = MODE != kScoresSelect && WAVES == kWaves;
   __shared__ __attribute__((aligned(16))) unsigned char stage[2][kTilesPerStep * kStageBytes];
@@ -593,19 +601,36 @@ __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void 
     // the tile's base is wave-uniform: only 32-bit lane offsets in vector registers
     const unsigned char* kc =
         kcorr + (size_t)__builtin_amdgcn_readfirstlane(t) * kKCorrTile;
+    auto half = [&](int part) {   // 0: <q_r, k>, 1: <q_g, k_r>
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      if (kk < 4 ? !do_q : !do_k) continue;   // kk 0-3: <q_r, k>; 4-7: <q_g, k_r>
-      const uint4 qa = has ? *(const uint4*)(qc + 32 * kk + 8 * gq) : make_uint4(0, 0, 0, 0);
+      for (int k2 = 0; k2 < 4; k2 += kResBatch) {
+        uint4 qa[kResBatch];
 #pragma unroll
-      for (int bk = 0; bk < 2; ++bk) {
-        const uint32_t off = (uint32_t)(bk * (kKCorrTile / 2) + kk * 1024) + (uint32_t)lane * 16u;
-        const uint4 kb = *(const uint4*)(kc + off);
-        corr[bk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qa),
-                                                          __builtin_bit_cast(bf16x8, kb),
-                                                          corr[bk], 0, 0, 0);
+        for (int kk = 0; kk < kResBatch; ++kk)
+          qa[kk] = has ? *(const uint4*)(qc + kHeadDim * part + 32 * (k2 + kk) + 8 * gq)
+                       : make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int b0 = 0; b0 < 2; b0 += kResVecs) {
+          uint4 kb[kResVecs][kResBatch];
+#pragma unroll
+          for (int kk = 0; kk < kResBatch; ++kk)
+#pragma unroll
+            for (int v = 0; v < kResVecs; ++v)
+              kb[v][kk] = *(const uint4*)(kc + (uint32_t)((b0 + v) * (kKCorrTile / 2) +
+                                                          (4 * part + k2 + kk) * 1024) +
+                                          (uint32_t)lane * 16u);
+#pragma unroll
+          for (int kk = 0; kk < kResBatch; ++kk)
+#pragma unroll
+            for (int v = 0; v < kResVecs; ++v)
+              corr[b0 + v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, qa[kk]), __builtin_bit_cast(bf16x8, kb[v][kk]),
+                  corr[b0 + v], 0, 0, 0);
+        }
       }
-    }
+    };
+    if (do_q) half(0);
+    if (do_k) half(1);
   };
 
   // Per tile: the staged key limbs and records, then for each row tile the
@@ -638,7 +663,7 @@ __global__ __launch_bounds__(WAVES * kWave, MODE == kScoresSelect ? 1 : 4) void 
       // A half is formed where its own bound passes tau / 2: the halves left
       // out together still move a logit by less than tau.  (Gated on R > 0, a
       // residual of 1e-13 in one element pulled in a whole half: 28 heads,
-      // 65536 tokens, spread key norms 458 us, now 316.)
+      // 65536 tokens, spread key norms 458 us, now 303.)
       const float half = 0.5f * tau;
       residual(kt, t, corr,
                __builtin_amdgcn_ballot_w64(fmaxf(k0.A, k1.A) * Rqm[kt] > half) != 0,
