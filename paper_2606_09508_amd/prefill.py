@@ -132,13 +132,17 @@ class Attention:
         return o
 
 
+def _kernel_device(dev) -> bool:
+    return dev.type == "cuda"
+
+
 def _plain(*ts) -> bool:
     """Whether a kernel call on these tensors computes all that the tensor
     operations would: ordinary tensors of one GPU, and nothing that the call
     would be invisible to (autograd, forward-mode and functorch transforms,
     tensor subclasses, a compiler's tracing)."""
     dev = ts[0].device
-    return (dev.type == "cuda"
+    return (_kernel_device(dev)
             and all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.device == dev for t in ts)
             and not torch.compiler.is_compiling()
             and torch._C._functorch.peek_interpreter_stack() is None
@@ -155,6 +159,13 @@ def _norm_fits(x, gain) -> bool:
     H = x.shape[-1]
     return (x.numel() > 0 and H % 8 == 0 and H <= 16384 and tuple(gain.shape) == (H,)
             and x.dtype == gain.dtype == torch.bfloat16 and _dense16(x, gain))
+
+
+def _adds(x, y) -> bool:
+    """Whether ei_add_rmsnorm forms the residual sum x + y as the tensor sum
+    would: y may carry gradients where x has none (an MLP or output projection
+    being trained in an otherwise frozen layer), and may broadcast."""
+    return _plain(x, y) and y.dtype == x.dtype and y.shape == x.shape and _dense16(y)
 
 
 def _one_pass(x, w, shape: DecoderShape, cos, sin) -> bool:
@@ -176,6 +187,8 @@ def _layer(x, y, w, shape: DecoderShape, attn: Attention, cos, sin, trace=None):
     takes their sum in the pass that reads it."""
     B, N, _ = x.shape
     Hq, Hkv, D = shape.n_q_heads, shape.n_kv_heads, shape.head_dim
+    if y is not None and not _adds(x, y):
+        x, y = x + y, None
     one_pass = _one_pass(x, w, shape, cos, sin)
     if one_pass:
         x, h = eb.add_rmsnorm(x, y, w["norm1"], shape.rms_eps)
@@ -193,7 +206,7 @@ def _layer(x, y, w, shape: DecoderShape, attn: Attention, cos, sin, trace=None):
     if trace is not None:
         trace.update(q=q.clone(), k=k.clone(), v=v.clone(), o=o.clone())
     y = o.transpose(1, 2).reshape(B, N, Hq * D) @ w["wo"]
-    if one_pass and _plain(x, y):   # (the attention may be a caller's own, with gradients)
+    if one_pass and _adds(x, y):   # (the attention may be a caller's own, with gradients)
         x, h = eb.add_rmsnorm(x, y, w["norm2"], shape.rms_eps)
         g = h @ w["w_gate"]
         m = eb.swiglu(g, h @ w["w_up"], out=g)

@@ -102,3 +102,17 @@ def test_layer_takes_tensor_operations_where_kernels_do_not_apply():
     xg = x.clone().requires_grad_()
     pf.layer_forward(xg, w, shape, attn, cos, sin).float().sum().backward()
     assert xg.grad is not None and bool(torch.isfinite(xg.grad.float()).all())
+
+
+def test_gradients_cross_into_a_frozen_layer():
+    """A trained MLP projection below a frozen layer: the frozen layer's norm
+    adds a summand with gradients, which the tensor sum records."""
+    dev = torch.device("cuda:0")
+    shape = pf.DecoderShape(hidden=512, n_q_heads=4, n_kv_heads=2, intermediate=1024)
+    layers = pf.make_weights(shape, 2, 5, dev)
+    layers[0]["w_down"].requires_grad_()
+    attn = pf.Attention(shape, 1, 256, "dense", pf.SparseConfig(), dev)
+    last, _ = pf.prefill(_rand((1, 256, 512), 9).cuda(), layers, shape, attn)
+    last.float().square().sum().backward()
+    grad = layers[0]["w_down"].grad.float()
+    assert bool(torch.isfinite(grad).all()) and float(grad.abs().max()) > 0.0

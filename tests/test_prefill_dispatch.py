@@ -1,0 +1,105 @@
+"""Which decoder layers run in the one-pass kernels and which in the tensor
+operations, on the CPU: the kernels are replaced by stand-ins that compute the
+same outside of autograd and of any tracing, as a call into the library does,
+and the device test is the CPU's.  Everything a tensor operation would record
+has to be recorded."""
+import pytest
+import torch
+
+from paper_2606_09508_amd import prefill as pf
+
+SHAPE = pf.DecoderShape(hidden=64, n_q_heads=2, n_kv_heads=1, intermediate=48, n_layers=2)
+N = 6
+
+
+def _opaque(fn, calls):
+    """fn as a library call sees it: on raw memory, recorded by nothing."""
+    def call(*args, **kw):
+        calls.append(fn.__name__)
+        with torch.no_grad():
+            return fn(*(a.detach() if isinstance(a, torch.Tensor) else a for a in args), **kw)
+    return call
+
+
+def _add_rmsnorm(x, y, gain, eps):
+    assert y is None or (y.shape == x.shape and y.dtype == x.dtype)
+    s = x if y is None else x + y
+    return s, pf._rmsnorm(s, gain, eps)
+
+
+def _rope_heads(q, k, v, cos, sin):
+    assert q.dtype == k.dtype == v.dtype == torch.bfloat16
+    q, k, v = (t.transpose(1, 2).contiguous() for t in (q, k, v))
+    return [pf._rope(q, cos, sin), pf._rope(k, cos, sin), v]
+
+
+def _swiglu(g, u, out=None):
+    return torch.nn.functional.silu(g) * u
+
+
+@pytest.fixture
+def kernels(monkeypatch):
+    """The stand-ins in the kernels' place; the list of the calls made."""
+    calls = []
+    for name, fn in (("add_rmsnorm", _add_rmsnorm), ("rope_heads", _rope_heads),
+                     ("swiglu", _swiglu)):
+        monkeypatch.setattr(pf.eb, name, _opaque(fn, calls))
+    monkeypatch.setattr(pf, "_kernel_device", lambda dev: dev.type == "cpu")
+    return calls
+
+
+def _attn(q, k, v):
+    """A caller's own attention, of tensor operations."""
+    g = q.shape[1] // k.shape[1]
+    k, v = (t.repeat_interleave(g, 1).float() for t in (k, v))
+    s = torch.matmul(q.float(), k.transpose(2, 3).contiguous()) / 128 ** 0.5
+    s = s.masked_fill(torch.ones(s.shape[-2:], dtype=torch.bool).triu(1), float("-inf"))
+    return torch.matmul(torch.softmax(s, -1), v).to(q.dtype)
+
+
+def _inputs(seed=0):
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn((1, N, SHAPE.hidden), generator=g).to(torch.bfloat16)
+    return x, pf.make_weights(SHAPE, 2, 3, torch.device("cpu"))
+
+
+def _same(a, b):
+    assert a.dtype == b.dtype and a.shape == b.shape
+    # (bf16 between the operations of two layers)
+    assert float((a.double() - b.double()).norm()) <= 2e-2 * float(b.double().norm())
+
+
+def test_plain_layers_take_the_kernels(kernels):
+    x, layers = _inputs()
+    with torch.no_grad():
+        pf.prefill(x, layers, SHAPE, _attn)
+    assert len(kernels) == 2 * 4 + 1   # two norms, rotary, SwiGLU a layer; the last norm
+
+
+@pytest.mark.parametrize("name", ["wo", "norm2", "w_gate", "w_up", "w_down"])
+def test_gradients_cross_into_a_frozen_layer(kernels, monkeypatch, name):
+    """One weight of the first layer is trained and the second layer is frozen:
+    the summand that the second layer's norm adds carries the gradient."""
+    x, layers = _inputs()
+    grads = []
+    for tensor_ops in (False, True):
+        if tensor_ops:
+            monkeypatch.setattr(pf, "_kernel_device", lambda dev: False)
+        w = layers[0][name] = layers[0][name].detach().requires_grad_()
+        last, _ = pf.prefill(x, layers, SHAPE, _attn)
+        assert last.requires_grad
+        last.float().square().sum().backward()
+        grads.append(w.grad)
+    _same(*grads)
+    assert float(grads[0].float().abs().max()) > 0.0
+
+
+@pytest.mark.parametrize("name", ["wo", "w_down"])
+def test_summand_that_broadcasts(kernels, monkeypatch, name):
+    """A projection to one column is added to every column, as x + y does."""
+    x, layers = _inputs()
+    layers[0][name] = layers[0][name][:, :1].contiguous()
+    with torch.no_grad():
+        got = pf.prefill(x, layers, SHAPE, _attn)[0]
+        monkeypatch.setattr(pf, "_kernel_device", lambda dev: False)
+        _same(got, pf.prefill(x, layers, SHAPE, _attn)[0])
