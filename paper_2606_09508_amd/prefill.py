@@ -24,6 +24,7 @@ import time
 from dataclasses import dataclass
 
 import torch
+from torch.utils._device import DeviceContext
 
 from . import binding as eb
 
@@ -136,17 +137,29 @@ def _kernel_device(dev) -> bool:
     return dev.type == "cuda"
 
 
+def _observed() -> bool:
+    """Whether something looks on at the single tensor operations, to which a
+    kernel call is invisible: a compiler's, the TorchScript or an fx tracer,
+    dispatch and function modes (a default device apart, which only concerns
+    factory functions), functorch and forward-mode transforms."""
+    C = torch._C
+    return (torch.compiler.is_compiling() or C._get_tracing_state() is not None
+            or C._len_torch_dispatch_stack() > 0
+            or (C._len_torch_function_stack() > 0
+                and any(type(m) is not DeviceContext
+                        for m in torch.overrides._get_current_function_mode_stack()))
+            or C._functorch.peek_interpreter_stack() is not None
+            or torch.autograd.forward_ad._current_level >= 0)
+
+
 def _plain(*ts) -> bool:
     """Whether a kernel call on these tensors computes all that the tensor
-    operations would: ordinary tensors of one GPU, and nothing that the call
-    would be invisible to (autograd, forward-mode and functorch transforms,
-    tensor subclasses, a compiler's tracing)."""
+    operations would: ordinary tensors of one GPU, no gradient to record and
+    nothing that looks on."""
     dev = ts[0].device
     return (_kernel_device(dev)
             and all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.device == dev for t in ts)
-            and not torch.compiler.is_compiling()
-            and torch._C._functorch.peek_interpreter_stack() is None
-            and torch.autograd.forward_ad._current_level < 0
+            and not _observed()
             and not (torch.is_grad_enabled() and any(t.requires_grad for t in ts)))
 
 

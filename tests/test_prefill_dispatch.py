@@ -5,6 +5,9 @@ and the device test is the CPU's.  Everything a tensor operation would record
 has to be recorded."""
 import pytest
 import torch
+from torch.fx.experimental.proxy_tensor import make_fx
+from torch.overrides import TorchFunctionMode
+from torch.utils._python_dispatch import TorchDispatchMode
 
 from paper_2606_09508_amd import prefill as pf
 
@@ -103,3 +106,52 @@ def test_summand_that_broadcasts(kernels, monkeypatch, name):
         got = pf.prefill(x, layers, SHAPE, _attn)[0]
         monkeypatch.setattr(pf, "_kernel_device", lambda dev: False)
         _same(got, pf.prefill(x, layers, SHAPE, _attn)[0])
+
+
+def _run(x, layers):
+    with torch.no_grad():
+        return pf.prefill(x, layers, SHAPE, _attn)[0]
+
+
+class _CountDispatch(TorchDispatchMode):
+    seen = 0
+
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        self.seen += func is torch.ops.aten.rsqrt.default
+        return func(*args, **(kwargs or {}))
+
+
+class _CountFunction(TorchFunctionMode):
+    seen = 0
+
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        self.seen += func is torch.rsqrt
+        return func(*args, **(kwargs or {}))
+
+
+@pytest.mark.parametrize("tracer", ["jit", "fx"])
+def test_tracers_record_every_operation(kernels, tracer):
+    """A layer traced with one input computes the layer of another one."""
+    x, layers = _inputs()
+    if tracer == "jit":
+        traced = torch.jit.trace(lambda t: _run(t, layers), x, check_trace=False)
+    else:
+        traced = make_fx(lambda t: _run(t, layers))(x)
+    assert kernels == []
+    other = _inputs(1)[0]
+    _same(traced(other), _run(other, layers))
+
+
+@pytest.mark.parametrize("mode", [_CountDispatch, _CountFunction])
+def test_modes_see_every_operation(kernels, mode):
+    x, layers = _inputs()
+    with mode() as m:
+        _run(x, layers)
+    assert kernels == [] and m.seen == 2 * 2 + 1   # the norms
+
+
+def test_default_device_keeps_the_kernels(kernels):
+    x, layers = _inputs()
+    with torch.device("cpu"):
+        _run(x, layers)
+    assert len(kernels) == 2 * 4 + 1
