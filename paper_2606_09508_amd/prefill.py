@@ -154,12 +154,15 @@ def _observed() -> bool:
 
 def _plain(*ts) -> bool:
     """Whether a kernel call on these tensors computes all that the tensor
-    operations would: ordinary tensors of one GPU, no gradient to record and
-    nothing that looks on."""
+    operations would: ordinary tensors of one GPU, no gradient to record,
+    nothing that looks on and no autocast to another type than bf16 (under
+    which the products between the kernels are of that type)."""
     dev = ts[0].device
     return (_kernel_device(dev)
             and all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.device == dev for t in ts)
             and not _observed()
+            and not (torch.is_autocast_enabled(dev.type)
+                     and torch.get_autocast_dtype(dev.type) != torch.bfloat16)
             and not (torch.is_grad_enabled() and any(t.requires_grad for t in ts)))
 
 

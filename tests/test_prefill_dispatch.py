@@ -155,3 +155,13 @@ def test_default_device_keeps_the_kernels(kernels):
     with torch.device("cpu"):
         _run(x, layers)
     assert len(kernels) == 2 * 4 + 1
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_autocast(kernels, monkeypatch, dtype):
+    """Under autocast the products are of its type, whatever the weights' is."""
+    x, layers = _inputs()
+    with torch.autocast("cpu", dtype=dtype):
+        got = _run(x, layers)
+        monkeypatch.setattr(pf, "_kernel_device", lambda dev: False)
+        _same(got, _run(x, layers))
