@@ -82,10 +82,19 @@ def make_weights(shape: DecoderShape, n_layers: int, seed: int, device) -> list[
     return layers
 
 
+def _tables_fit(N, D, theta) -> bool:
+    """Values ei_rope_tables takes as they are: 32-bit sizes, and a theta that
+    is a normal fp32 number."""
+    f = torch.finfo(torch.float32)
+    return (type(N) is int and type(D) is int and type(theta) in (int, float)
+            and 0 < N < 2 ** 31 and 0 < D < 2 ** 31 and f.tiny <= theta <= f.max)
+
+
 def rope_tables(N: int, D: int, theta: float, device):
     """cos / sin [N, D/2] (fp32) of the rotary embedding, half-split layout."""
-    if type(N) is int and type(D) is int and type(theta) in (int, float) and N > 0 and D > 0 \
-            and theta > 0 and torch.device(device).type == "cuda":
+    # (device may be anything a factory function takes)
+    if _tables_fit(N, D, theta) and not _observed() \
+            and _kernel_device(torch.empty(0, device=device).device):
         cos, sin = (torch.empty((N, (D + 1) // 2), dtype=torch.float32, device=device)
                     for _ in range(2))
         if _plain(cos, sin):

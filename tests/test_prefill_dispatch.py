@@ -3,6 +3,8 @@ operations, on the CPU: the kernels are replaced by stand-ins that compute the
 same outside of autograd and of any tracing, as a call into the library does,
 and the device test is the CPU's.  Everything a tensor operation would record
 has to be recorded."""
+import ctypes
+
 import pytest
 import torch
 from torch.fx.experimental.proxy_tensor import make_fx
@@ -40,12 +42,20 @@ def _swiglu(g, u, out=None):
     return torch.nn.functional.silu(g) * u
 
 
+def _tables(cos, sin, head_dim, theta):
+    assert 0 < cos.shape[0] < 2 ** 31 and 0 < ctypes.c_float(theta).value < float("inf")
+    inv = 1.0 / (theta ** (torch.arange(0, head_dim, 2, dtype=torch.float32) / head_dim))
+    ang = torch.arange(cos.shape[0], dtype=torch.float32)[:, None] * inv
+    cos.copy_(torch.cos(ang))
+    sin.copy_(torch.sin(ang))
+
+
 @pytest.fixture
 def kernels(monkeypatch):
     """The stand-ins in the kernels' place; the list of the calls made."""
     calls = []
     for name, fn in (("add_rmsnorm", _add_rmsnorm), ("rope_heads", _rope_heads),
-                     ("swiglu", _swiglu)):
+                     ("swiglu", _swiglu), ("rope_tables", _tables)):
         monkeypatch.setattr(pf.eb, name, _opaque(fn, calls))
     monkeypatch.setattr(pf, "_kernel_device", lambda dev: dev.type == "cpu")
     return calls
@@ -76,7 +86,7 @@ def test_plain_layers_take_the_kernels(kernels):
     x, layers = _inputs()
     with torch.no_grad():
         pf.prefill(x, layers, SHAPE, _attn)
-    assert len(kernels) == 2 * 4 + 1   # two norms, rotary, SwiGLU a layer; the last norm
+    assert len(kernels) == 2 * 4 + 2   # two norms, rotary, SwiGLU a layer; tables, last norm
 
 
 @pytest.mark.parametrize("name", ["wo", "norm2", "w_gate", "w_up", "w_down"])
@@ -154,7 +164,7 @@ def test_default_device_keeps_the_kernels(kernels):
     x, layers = _inputs()
     with torch.device("cpu"):
         _run(x, layers)
-    assert len(kernels) == 2 * 4 + 1
+    assert len(kernels) == 2 * 4 + 2
 
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
@@ -165,3 +175,20 @@ def test_autocast(kernels, monkeypatch, dtype):
         got = _run(x, layers)
         monkeypatch.setattr(pf, "_kernel_device", lambda dev: False)
         _same(got, _run(x, layers))
+
+
+@pytest.mark.parametrize("device", [None, "cpu", torch.device("cpu")], ids=str)
+@pytest.mark.parametrize("theta", [1e4, 500000, 1e-46, 1e39])
+def test_rope_tables_arguments(monkeypatch, device, theta):
+    """Every device and theta the tensor operations take."""
+    ref = pf.rope_tables(3, 128, theta, torch.device("cpu"))
+    monkeypatch.setattr(pf, "_kernel_device", lambda dev: dev.type == "cpu")
+    monkeypatch.setattr(pf.eb, "rope_tables", _tables)
+    for a, b in zip(pf.rope_tables(3, 128, theta, device), ref):
+        assert torch.equal(a.nan_to_num(), b.nan_to_num()) and a.dtype == b.dtype
+
+
+@pytest.mark.parametrize("N,D", [(2 ** 31, 2), (2 ** 32 + 5, 2), (1, 2 ** 31), (0, 128)])
+def test_rope_tables_of_64_bit_sizes_stay_off_the_kernel(N, D):
+    """(ei_rope_tables counts positions and dimensions in 32 bits.)"""
+    assert not pf._tables_fit(N, D, 1e4) and pf._tables_fit(2 ** 31 - 1, 128, 1e4)
