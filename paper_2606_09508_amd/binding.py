@@ -12,6 +12,7 @@ import contextlib
 import ctypes
 import functools
 import math
+import operator
 import os
 
 import torch
@@ -211,12 +212,17 @@ def num_blocks(N: int, block_len: int) -> int:
     return -(-N // block_len)
 
 
-@functools.lru_cache(maxsize=256, typed=True)   # a pure function of its sizes
-def kmax(seg_len: int, block_len: int, base_budget: int = 2048, mult: int = 3) -> int:
+@functools.lru_cache(maxsize=256)   # a pure function of four plain integers
+def _kmax(seg_len: int, block_len: int, base_budget: int, mult: int) -> int:
     v = lib().ei_kmax(Tiling(seg_len, block_len), budget_params(base_budget=base_budget, mult=mult))
     if v < 0:
         raise ValueError("invalid tiling or budget parameters")
     return v
+
+
+def kmax(seg_len: int, block_len: int, base_budget: int = 2048, mult: int = 3) -> int:
+    # (numbers of other kinds, arrays and tensors among them, by their value)
+    return _kmax(operator.index(seg_len), operator.index(block_len), int(base_budget), int(mult))
 
 
 def probe_workspace_bytes(dims: Dims, seg_len: int, block_len: int) -> int:

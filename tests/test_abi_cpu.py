@@ -5,7 +5,9 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
+import torch
 
 from paper_2606_09508_amd import binding as eb
 
@@ -39,6 +41,12 @@ def test_helpers(L):
     assert eb.kmax(128, 64, 2048, 3) == 98
     assert eb.kmax(2048, 64, 2048, 3) == 96 + 32
     assert eb.kmax(256, 128, 256, 3) == 6 + 2
+    # numbers of any kind count by their value at the call
+    assert eb.kmax(np.array(128), 64, np.float32(2048), 3) == 98
+    budget = torch.tensor(2048)
+    assert eb.kmax(128, 64, budget) == 98
+    budget.fill_(256)
+    assert eb.kmax(128, 64, budget) == 14
     d = eb.Dims(1, 32, 8, 131072, 128)
     assert L.ei_num_segments(d, eb.Tiling(128, 64)) == 1024
     assert L.ei_num_blocks(d, eb.Tiling(128, 64)) == 2048
