@@ -36,13 +36,14 @@
  *    boundary, fp32 / int32 arrays on a 4-byte one (hipMalloc returns
  *    256-byte aligned memory); a pointer that is not returns
  *    EI_ERR_UNSUPPORTED.
- *  - Outputs must not alias inputs.  Identical inputs give bitwise-identical
- *    outputs (the only atomics are integer counts: in LDS, and the sparse
- *    attention's work-queue counters in its workspace, which decide which
- *    workgroup computes a tile but not what it computes).  No global state
- *    (except the no-allocation variant's scratch array), no logging; calls
- *    on different streams may run concurrently when they do not share a
- *    workspace.
+ *  - Outputs must not alias inputs, except where an entry point says that one
+ *    may (ei_add_rmsnorm, ei_swiglu).
+ *  - Identical inputs give bitwise-identical outputs (the only atomics are
+ *    integer counts: in LDS, and the sparse attention's work-queue counters in
+ *    its workspace, which decide which workgroup computes a tile but not what
+ *    it computes).  No global state (except the no-allocation variant's
+ *    scratch array), no logging; calls on different streams may run
+ *    concurrently when they do not share a workspace.
  */
 #ifndef ENTROPYINFER_H
 #define ENTROPYINFER_H

@@ -59,12 +59,13 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // T threads per row (a wave for rows of up to 1024 columns, which leaves no
-// barrier; else the workgroup), CH chunks of 8 columns per thread.
+// barrier; else the workgroup), CH chunks of 8 columns per thread.  sum_out
+// may be x or y (so none of the three is restrict): a thread stores a chunk
+// after it has loaded its chunks of both.
 template <int T, int CH, bool ADD>
 __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ y,
-    const uint16_t* __restrict__ gain, int64_t rows, int cols, float eps,
-    uint16_t* __restrict__ sum_out, uint16_t* __restrict__ out) {
+    const uint16_t* x, const uint16_t* y, const uint16_t* __restrict__ gain, int64_t rows,
+    int cols, float eps, uint16_t* sum_out, uint16_t* __restrict__ out) {
   __shared__ float part[kThreads / kWave];
   const int t = threadIdx.x % T;
   const int64_t row = (int64_t)blockIdx.x * (kThreads / T) + threadIdx.x / T;

@@ -40,6 +40,18 @@ def test_add_rmsnorm(rows, cols):
         _close(h, d * torch.rsqrt((d * d).mean(-1, keepdim=True) + 1e-5) * g.double())
 
 
+@pytest.mark.parametrize("cols", [520, 4096, 16384])   # a wave's row, a workgroup's, the longest
+@pytest.mark.parametrize("into", ["x", "y"])
+def test_add_rmsnorm_in_place(cols, into):
+    """The C entry writing the sum over one of its operands."""
+    x, y, g = (_rand(s, i).cuda() for i, s in enumerate([(3, cols), (3, cols), (cols,)]))
+    s_ref, h_ref = eb.add_rmsnorm(x, y, g, 1e-5)
+    s, h = (x if into == "x" else y), torch.empty_like(x)
+    assert eb.lib().ei_add_rmsnorm(x.data_ptr(), y.data_ptr(), g.data_ptr(), 3, cols, 1e-5,
+                                   s.data_ptr(), h.data_ptr(), eb._stream(x)) == 0
+    assert torch.equal(s, s_ref) and torch.equal(h, h_ref)
+
+
 @pytest.mark.parametrize("N,D,theta", [(1, 128, 500000.0), (3, 2, 10000.0), (1000, 128, 500000),
                                        (131072, 128, 500000.0), (257, 96, 1e4)])
 def test_rope_tables(N, D, theta):
