@@ -90,6 +90,17 @@ def test_swiglu(n):
     assert torch.equal(gg.nan_to_num(), out.nan_to_num())
 
 
+def test_swiglu_is_the_tensor_operation():
+    """Every bf16 value of g: the same fp32 operations, so bitwise equal."""
+    g = torch.arange(1 << 16, dtype=torch.int32).to(torch.int16).view(torch.bfloat16).cuda()
+    u = _rand((1 << 16,), 3).cuda()
+    ref = torch.nn.functional.silu(g) * u
+    out = eb.swiglu(g, u)
+    assert torch.equal(out.isnan(), ref.isnan())
+    ok = ~ref.isnan()
+    assert torch.equal(out[ok].view(torch.int16), ref[ok].view(torch.int16))
+
+
 def test_layer_takes_tensor_operations_where_kernels_do_not_apply():
     """Autograd still reaches the hidden state, and a layer of fp32 tables in
     another layout gives the same result as the one-pass kernels."""
