@@ -270,9 +270,12 @@ ei_status ei_probe_select_fused(const uint16_t* q, const uint16_t* k, ei_dims di
  * heaviest tiles first, then taking items from the other XCDs' queues; K/V
  * blocks then stay in the L2 of the XCD whose tiles select them.  Otherwise
  * one workgroup per (tile, query head) on a static grid.  A launch of at most
- * 128 tiles of 128 queries, with or without a workspace, shares each tile's
- * keys out over the waves of a workgroup and merges their sums (the same for
- * dense attention and the GQA-union entry).
+ * 128 tiles of 128 queries whose tiles have enough keys for it, with or without
+ * a workspace, shares each tile's keys out over the waves of a workgroup and
+ * merges their sums (the same for dense attention and the GQA-union entry).
+ * That choice follows from B, Hq, N, kmax, L_B and the mode, so the bits of one
+ * sequence's output depend on the launch it is part of (the batch it is in),
+ * by roundings of the probabilities and sums, not on anything else.
  *
  * Errors: EI_ERR_NULL, EI_ERR_SHAPE (also kmax <= 0 or a softmax_scale that is
  * not finite and positive), EI_ERR_UNSUPPORTED (also a workspace not 16-byte

@@ -39,8 +39,8 @@
 // for KV-group counts that do not tile the XCDs) the grid is static: the KV
 // groups rotate over the XCDs every 4 tiles, heaviest tiles first.
 //
-// Launches of few tiles (attn_split_kernel) split each tile's keys over the
-// waves instead, dense and sparse alike.
+// Launches of few tiles (attn_split_kernel; the rule is at split_tiles) split
+// each tile's keys over the waves instead, dense and sparse alike.
 #include "ei_internal.h"
 
 #include <math.h>
@@ -622,7 +622,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(
 // copies only, the next step's K copied once this step's scores have been
 // read, its V after the last product); the four partial (m, l, O) are merged
 // through LDS at the end.  The same rows, blocks and arithmetic per step as
-// attn_kernel, so the result differs only by the order of the sums.
+// attn_kernel; the result differs by the order of the sums and by the rounding
+// of the probabilities to bf16, against the wave's own running maximum.
 constexpr int kSplitWaves = kThreads / kWave;
 constexpr int kSplitTileQ = 32;
 
@@ -786,18 +787,39 @@ __global__ __launch_bounds__(kThreads, 1) void attn_split_kernel(
   }
 }
 
-// The split takes a launch of at most kSplitMaxTiles 128-row tiles (half the
-// CUs).  Its 32-row tiles are four times as many, one to a CU (128 KB of LDS),
-// and each copies its keys for itself, so it stops paying once the 128-row
-// tiles fill the chip.  128-row against 32-row split tiles: 4 heads, 1024
-// tokens (32 tiles) 24.8 / 15.4 us, 2048 (64) 44.3 / 19.2, 4096 (128) 82.9 /
-// 38.3; dense, 4 heads, 4096 tokens (128) causal 80.3 / 35.8, full 80.8 / 51.1;
-// 16 heads, 900 tokens (128) 21.5 / 16.9; but 32 heads, 896 tokens (224) 22.0 /
-// 28.8.  (At 128 tiles a wave has at most 64 steps, one list entry per lane.)
-constexpr int kSplitMaxTiles = 128;
+// Which launches take the split.  Its 32-row tiles run one to a CU (128 KB of
+// LDS) and each copies its keys for itself, so the choice lies with the rounds
+// they make on the CUs and the steps a tile has (us, 128-row / split tiles):
+//  - up to 128 tokens, over all keys 96: little to share out (64 tokens 5.0 /
+//    6.1; 8 heads, 120 causal 6.7 / 6.7, 80 over all keys 6.5 / 6.6).  Lists
+//    would gain from 97 (7.3 / 7.1), but a sparse launch follows the causal one
+//    wherever its lists can hold every block: the two are then bitwise equal;
+//  - one round: from there always (16 heads, 129 causal 7.0 / 6.5, 512 14.6 /
+//    9.0; 4 heads, 2048 42.9 / 18.9; over lists of six steps 12.9 / 9.3; 8
+//    heads, 97 tokens, all keys 7.2 / 6.6);
+//  - two rounds (at most kSplitMaxTiles 128-row tiles, half the CUs): the
+//    second has to be paid for by the steps that a wave does not make.  Causal
+//    tiles pay from 9 (7: 32 heads, 400 tokens 12.3 / 13.7; 8: 28 heads, 512
+//    15.0 / 14.2, 481 14.3 / 14.1; 9: 16 heads, 517 14.6 / 11.6; 64: 4 heads,
+//    4096 82 / 40), tiles over all keys, equally long, from 14 (9: 16 heads, 517
+//    16.5 / 17.9; 13: 769 21.4 / 21.2; 15: 900 23.9 / 21.7; 64: 4 heads, 4096
+//    81 / 55).  Lists of capacity C steps hold C / 3 and more at the default
+//    cap; those far shorter than the sequence are as equal as full tiles, with
+//    few steps (C = 14: 8 heads, 1531 tokens 23.3 / 19.4, 2048 21.1 / 21.5, 1
+//    head, 16384 14.0 / 18.2; C = 26: 2 heads, 5000 37.8 / 27.7, 1 head, 16384
+//    19.3 / 22.5; C = 98: 1 head, 16384 49.5 / 43.3).
+constexpr int kSplitMaxTiles = 128, kSplitRound = 2 * kSplitMaxTiles;
 static_assert(kSplitMaxTiles * kTileQ / kSub <= kSplitWaves * kWave, "a lane per step of a wave");
+template <int MODE, int SUB>
 bool split_tiles(const AttnShape& s) {
-  return (int64_t)s.B * s.Hq * ((s.N + kTileQ - 1) / kTileQ) <= kSplitMaxTiles;
+  const int64_t rows = (int64_t)s.B * s.Hq, steps = (s.N + kSub - 1) / kSub;
+  if (rows * ((s.N + kTileQ - 1) / kTileQ) > kSplitMaxTiles ||
+      s.N <= (MODE == kDenseFull ? 96 : 128))
+    return false;
+  if (rows * ((s.N + kSplitTileQ - 1) / kSplitTileQ) <= kSplitRound) return true;
+  if (steps < (MODE == kDenseFull ? 14 : 9)) return false;
+  const int64_t cap = (int64_t)s.kmax * SUB;
+  return MODE != kSparse || (cap >= 9 && steps <= (cap < 24 ? 2 : 4) * cap);
 }
 
 template <int MODE, int SUB>
@@ -847,7 +869,7 @@ template <int MODE, int SUB>
 hipError_t launch_t(const uint16_t* q, const uint16_t* k, const uint16_t* v, const AttnShape& s,
                     const int32_t* bidx, const int32_t* bcnt, uint16_t* o, uint32_t* sched,
                     bool sched_zeroed, hipStream_t stream) {
-  if (split_tiles(s)) return launch_split_t<MODE, SUB>(q, k, v, s, bidx, bcnt, o, stream);
+  if (split_tiles<MODE, SUB>(s)) return launch_split_t<MODE, SUB>(q, k, v, s, bidx, bcnt, o, stream);
   const int n_tiles = (s.N + kTileQ - 1) / kTileQ;
   const int64_t total = (int64_t)s.B * s.Hq * n_tiles;
   int64_t grid = (total + kXcds - 1) / kXcds * kXcds;
@@ -1024,7 +1046,7 @@ hipError_t launch_union_t(const uint16_t* q, const uint16_t* k, const uint16_t* 
                           const AttnShape& s, const int32_t* bidx, const int32_t* bcnt,
                           uint16_t* o, hipStream_t stream) {
   // (bitwise the per-head kernel's output, so also the same kernel here)
-  if (split_tiles(s)) return launch_split_t<kSparse, SUB>(q, k, v, s, bidx, bcnt, o, stream);
+  if (split_tiles<kSparse, SUB>(s)) return launch_split_t<kSparse, SUB>(q, k, v, s, bidx, bcnt, o, stream);
   const int n_tiles = (s.N + kTileQ - 1) / kTileQ;
   const int npair = (s.Hq / s.Hkv + 1) / 2;
   const int64_t grid = (int64_t)s.B * s.Hkv * npair * n_tiles;

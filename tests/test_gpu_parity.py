@@ -313,9 +313,9 @@ def test_last_128_block_past_the_end(N):
 @pytest.mark.parametrize("N", [1, 31, 33, 64, 97, 129, 1000, 2048, 4096])
 @pytest.mark.parametrize("tiling", [(128, 64), (256, 128)])
 def test_split_tiles_equal_large_launch(N, tiling):
-    """A launch of at most 128 tiles takes the kernel whose waves share a
-    tile's keys out and merge their sums; five batch entries of the same heads
-    (or one more head at 4096 tokens) take the ordinary one.  Dense causal,
+    """A launch of at most 128 tiles of enough steps takes the kernel whose
+    waves share a tile's keys out and merge their sums; five batch entries of
+    the same heads (two at 4096 tokens) take the ordinary one.  Dense causal,
     dense full and sparse (lists without the first block, gaps, an empty list)
     agree to bf16 rounding, and with the oracle."""
     Hq, Hkv = 4, 2
@@ -363,6 +363,58 @@ def test_split_tiles_equal_large_launch(N, tiling):
             ref[empty] = 0.0
         err = np.abs(bf16_to_f64(o)[rows[:, 0], rows[:, 1], rows[:, 2]] - ref)
         assert err.max() <= ATTN_ABS, (mode, err.max())
+
+
+@pytest.mark.parametrize("Hq,Hkv,N,mode", [
+    (16, 16, 517, "full"), (16, 4, 545, "full"),      # two rounds of three steps a wave
+    (32, 8, 400, "causal"), (28, 4, 300, "full"), (64, 8, 130, "causal"),
+    (4, 1, 100, "causal"), (8, 2, 66, "full"),        # two steps
+    (28, 4, 300, "sparse"), (64, 8, 256, "sparse"),
+    (1, 1, 16384, "sparse"),                          # lists far shorter than the sequence
+])
+def test_split_leaves_short_tiles_alone(Hq, Hkv, N, mode):
+    """Launches of at most 128 tiles whose split tiles make a second round of
+    few steps, or have too few to share out, take the ordinary kernel (the
+    split is slower there): bitwise what a batch too large for the split gives."""
+    w = synth.make("c1", 31, Hq=Hq, Hkv=Hkv, N=N)
+    q, k, v = to_dev(w.q), to_dev(w.k), to_dev(w.v)
+    CS, r = -(-N // 128), 2
+    km = 16                                           # (three of the past, the segment's own)
+    idx = np.full((1, Hq, CS, km), -1, np.int32)
+    cnt = np.zeros((1, Hq, CS), np.int32)
+    for s in range(CS):
+        blk = sorted({b for b in (0, s * r // 2, s * r - 1) if 0 <= b < s * r}) + \
+            list(range(s * r, min((s + 1) * r, -(-N // 64))))
+        idx[0, :, s, :len(blk)], cnt[0, :, s] = blk, len(blk)
+
+    def run(reps):
+        t = [torch.from_numpy(x).cuda() if isinstance(x, np.ndarray) else x
+             for x in (q, k, v, idx, cnt)]
+        q_, k_, v_, i_, c_ = (x.repeat(reps, *([1] * (x.dim() - 1))).contiguous() for x in t)
+        if mode == "sparse":
+            return eb.sparse_prefill_attn(q_, k_, v_, i_, c_, 128, 64, w.softmax_scale)
+        return eb.dense_prefill_attn(q_, k_, v_, w.softmax_scale, mode == "causal")
+    reps = 128 // (Hq * CS) + 1
+    small, large = run(1), run(reps)
+    torch.cuda.synchronize()
+    assert Hq * CS <= 128 < reps * Hq * CS
+    assert torch.equal(small[0], large[0]) and torch.equal(small[0], large[reps - 1])
+
+
+@pytest.mark.parametrize("Hq,N", [(4, 97), (4, 128), (4, 129), (32, 400), (28, 512), (16, 513),
+                                  (16, 900), (2, 5000)])
+@pytest.mark.parametrize("Lb", [64, 128])
+def test_all_blocks_sparse_is_dense_across_the_split(Hq, N, Lb):
+    """Lists that hold every block, in rows of exactly that capacity, give the
+    dense causal output bit for bit: both launches make the same choice."""
+    w = synth.make("c1", 2, Hq=Hq, Hkv=2, N=N)
+    q, k, v = to_dev(w.q), to_dev(w.k), to_dev(w.v)
+    CS, CB, r = -(-N // 128), -(-N // Lb), 128 // Lb
+    vis = torch.arange(1, CS + 1) * r
+    cnt = vis.clamp(max=CB).int().expand(1, Hq, CS).contiguous().cuda()
+    idx = torch.arange(CB, dtype=torch.int32).expand(1, Hq, CS, CB).contiguous().cuda()
+    o = eb.sparse_prefill_attn(q, k, v, idx, cnt, 128, Lb, w.softmax_scale)
+    assert torch.equal(o, eb.dense_prefill_attn(q, k, v, w.softmax_scale, True))
 
 
 def test_deterministic():
