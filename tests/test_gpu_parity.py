@@ -107,6 +107,42 @@ def check_attention(w, r, rows=None):
     return float(err.max()), float(err.mean())
 
 
+def n_items(w):
+    """128-row tiles of an attention launch."""
+    return w.B * w.Hq * -(-w.N // 128)
+
+
+def repeated(w, more_than, *ts):
+    """The tensors with the batch repeated until an attention launch has more
+    than that many tiles: 128 leave the kernel that shares a tile's keys out
+    over its waves, twice the CUs make the persistent schedule queue (eight
+    entries and multiples of it divide its KV groups over the XCDs)."""
+    reps = (more_than // n_items(w) // 8 + 1) * 8
+    assert reps * n_items(w) > more_than
+    return [t.repeat(reps, *([1] * (t.dim() - 1))).contiguous() for t in ts]
+
+
+def queue_items():
+    return 2 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def large_launches(w, q, k, v, idx, cnt):
+    """The sparse attention's output for w in launches too large for the split:
+    per-head on the static grid, per-head queued, and GQA-union, which have to
+    agree bit for bit in every copy of the batch."""
+    outs = []
+    for more_than, kw in ((128, dict(persistent=False)), (queue_items(), dict(persistent=True)),
+                          (128, dict(gqa_union=True))):
+        if kw.get("gqa_union") and (idx.shape[-1] > 128 or w.CB > 8192):
+            continue   # (lists and blocks the union mode does not take)
+        t = repeated(w, more_than, q, k, v, idx, cnt)
+        o = eb.sparse_prefill_attn(*t, w.Ls, w.Lb, w.softmax_scale, **kw)
+        outs += o.split(w.B)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, outs[0]) for o in outs[1:])
+    return outs[0]
+
+
 C1_CASES = [
     dict(),                                           # the tiny workload itself
     dict(N=1000),                                     # ragged tail
@@ -138,6 +174,8 @@ def test_path_parity_small(case, seed):
     hrel, lerr = check_probe(w, r)
     check_select(w, r)
     amax, amean = check_attention(w, r)
+    idx, cnt = (torch.from_numpy(r["sel"][n]).cuda() for n in ("idx", "cnt"))
+    check_attention(w, dict(r, o=large_launches(w, r["q"], r["k"], r["v"], idx, cnt)))
     say(f"  entropy rel {hrel:.2e}  logscore abs {lerr:.2e}  attn max {amax:.2e} mean {amean:.2e}")
 
 
@@ -267,30 +305,35 @@ def test_dense_attention_running_max_jumps(causal):
     """The running maximum is left behind by more than the probabilities'
     2^32 limit, and by enough to overflow exp2, in the middle of rows: the
     kernel must take the row maxima and rescale; every row against the fp64
-    oracle."""
+    oracle, in a launch that takes the split and in one that does not."""
     w = _jump_inputs()
     say(f"[dense jumps] causal={causal}")
-    o = eb.dense_prefill_attn(to_dev(w.q), to_dev(w.k), to_dev(w.v), w.softmax_scale, causal)
-    torch.cuda.synchronize()
+    qkv = [to_dev(x) for x in (w.q, w.k, w.v)]
     rows = np.array([[0, h, i] for h in range(w.Hq) for i in range(w.N)], np.int32)
     ref = oracle.attention(w.q, w.k, w.v, rows, w.softmax_scale, causal)
-    got = bf16_to_f64(o)[rows[:, 0], rows[:, 1], rows[:, 2]]
-    assert np.isfinite(got).all()
-    assert np.abs(got - ref).max() <= ATTN_ABS
+    for t in (qkv, repeated(w, 128, *qkv)):
+        o = eb.dense_prefill_attn(*t, w.softmax_scale, causal)
+        torch.cuda.synchronize()
+        got = bf16_to_f64(o[-1:])[rows[:, 0], rows[:, 1], rows[:, 2]]
+        assert np.isfinite(got).all()
+        assert np.abs(got - ref).max() <= ATTN_ABS
 
 
 def test_sparse_attention_running_max_jumps():
     """The same inputs through probe, selection and sparse attention: every
-    row against the oracle on the GPU's block lists."""
+    row against the oracle on the GPU's block lists, in a launch that takes the
+    split and in larger ones of every kernel."""
     w = _jump_inputs()
     say("[sparse jumps]")
     r = run_path(w)
     rows = np.array([[0, h, i] for h in range(w.Hq) for i in range(w.N)], np.int32)
     ref = oracle.attention(w.q, w.k, w.v, rows, w.softmax_scale, True, r["sel"]["idx"],
                            r["sel"]["cnt"], w.Ls, w.Lb)
-    got = bf16_to_f64(r["o"])[rows[:, 0], rows[:, 1], rows[:, 2]]
-    assert np.isfinite(got).all()
-    assert np.abs(got - ref).max() <= ATTN_ABS
+    idx, cnt = (torch.from_numpy(r["sel"][n]).cuda() for n in ("idx", "cnt"))
+    for o in (r["o"], large_launches(w, r["q"], r["k"], r["v"], idx, cnt)):
+        got = bf16_to_f64(o)[rows[:, 0], rows[:, 1], rows[:, 2]]
+        assert np.isfinite(got).all()
+        assert np.abs(got - ref).max() <= ATTN_ABS
 
 
 @pytest.mark.parametrize("N", [1281, 1300, 1344, 1345, 1407])
@@ -349,7 +392,8 @@ def test_split_tiles_equal_large_launch(N, tiling):
         ob = run(*(big(t) for t in (q, k, v, idx_t, cnt_t)))
         torch.cuda.synchronize()
         small, large = o[0].float(), ob[0].float()
-        # Both round each probability to bf16 (2^-9 of it) against a running
+        # Both round each probability to bf16 (by up to 2^-8 of it, over a row's
+        # keys by less than 2^-9 of their sum) against a running
         # maximum of their own, so each output, a mean of v weighted by the
         # probabilities, moves by at most 2^-9 max |v| in either; their own
         # rounding to bf16 is half a step (2^-8) in either.
@@ -363,6 +407,48 @@ def test_split_tiles_equal_large_launch(N, tiling):
             ref[empty] = 0.0
         err = np.abs(bf16_to_f64(o)[rows[:, 0], rows[:, 1], rows[:, 2]] - ref)
         assert err.max() <= ATTN_ABS, (mode, err.max())
+
+
+@pytest.mark.parametrize("N", [16384, 16384 - 77])
+@pytest.mark.parametrize("tiling", [(128, 64), (256, 128)])
+def test_split_long_rows(N, tiling):
+    """One head at the split's longest rows, 64 steps a wave: every lane of a
+    wave holds a list entry.  V is 1 in dim (step mod 128) of a step's 64 keys
+    and 0 elsewhere, so each output is the probability of at most two steps
+    and a step left out, visited twice or taken for another shows in full."""
+    Ls, Lb = tiling
+    CS, CB, r = -(-N // Ls), -(-N // Lb), Ls // Lb
+    w = synth.make("c1", 31, Hq=1, Hkv=1, N=N, Ls=Ls, Lb=Lb)
+    q, k = to_dev(w.q), to_dev(w.k)
+    step = torch.arange(N) // 64
+    v = torch.nn.functional.one_hot(step % 128, 128)[None, None].to(torch.bfloat16).cuda()
+    rng = np.random.default_rng(N)
+    idx = np.full((1, 1, CS, CB), -1, np.int32)
+    cnt = np.zeros((1, 1, CS), np.int32)
+    for s in range(CS):
+        past = np.flatnonzero(rng.random(s * r) < 0.8)
+        blk = np.concatenate([past, np.arange(s * r, min((s + 1) * r, CB))])
+        idx[0, 0, s, :len(blk)], cnt[0, 0, s] = blk, len(blk)
+    assert cnt.max() * Lb // 64 > 192   # list entries for lanes past 48
+    ts = [q, k, v, torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda()]
+    rows = np.array([[0, 0, i] for i in range(5, N, 397)] + [[0, 0, N - 1]], np.int32)
+    vb = synth.to_bf16_bits(v.float().cpu().numpy())
+    # Half a bf16 step (2^-8 of the value) for the probabilities and for the
+    # output, and 1% of both for fp32 scores and sums.
+    one = 1.01 * 2 * 2.0 ** -8
+    for mode in ("causal", "full", "sparse"):
+        outs = []
+        for t in (ts, [x.repeat(2, *([1] * (x.dim() - 1))) for x in ts]):
+            if mode == "sparse":
+                outs.append(eb.sparse_prefill_attn(*t, Ls, Lb, w.softmax_scale))
+            else:
+                outs.append(eb.dense_prefill_attn(*t[:3], w.softmax_scale, mode == "causal"))
+        small, large = outs[0][0].float(), outs[1][1].float()
+        assert bool(((small - large).abs() <= 2 * one * large).all()), mode
+        args = (idx, cnt, Ls, Lb) if mode == "sparse" else ()
+        ref = oracle.attention(w.q, w.k, vb, rows, w.softmax_scale, mode != "full", *args)
+        got = bf16_to_f64(outs[0])[rows[:, 0], rows[:, 1], rows[:, 2]]
+        assert (np.abs(got - ref) <= one * ref).all(), mode
 
 
 @pytest.mark.parametrize("Hq,Hkv,N,mode", [
@@ -441,7 +527,8 @@ def test_deterministic():
 ], ids=lambda x: x if isinstance(x, str) else None)
 def test_gqa_union_attention_equals_per_head(wl, seed, case):
     """GQA-union tiles (two heads of a KV group share each union block's copy)
-    give bitwise the per-head kernel's output."""
+    give bitwise the per-head kernel's output; a small case also in a launch
+    of more than 128 tiles, from which on the two are different kernels."""
     w = synth.make(wl, seed, **case)
     say(f"[union] {wl} seed={seed} {case}")
     q, k, v = to_dev(w.q), to_dev(w.k), to_dev(w.v)
@@ -462,31 +549,38 @@ def test_gqa_union_attention_equals_per_head(wl, seed, case):
         rows = _spread_query_rows(w, 3072, seed=seed)
     ref = oracle.attention(w.q, w.k, w.v, rows, w.softmax_scale, True, sel["idx"].cpu().numpy(),
                            sel["cnt"].cpu().numpy(), w.Ls, w.Lb)
-    got = bf16_to_f64(ou)[rows[:, 0], rows[:, 1], rows[:, 2]]
-    err = np.abs(got - ref)
-    say(f"  union vs oracle: {len(rows)} rows, max-abs {err.max():.2e} mean {err.mean():.2e}")
-    assert err.max() <= ATTN_ABS
+    outs = [ou]
+    if n_items(w) <= 128:
+        outs.append(large_launches(w, q, k, v, sel["idx"], sel["cnt"]))
+    for o in outs:
+        got = bf16_to_f64(o)[rows[:, 0], rows[:, 1], rows[:, 2]]
+        err = np.abs(got - ref)
+        say(f"  union vs oracle: {len(rows)} rows, max-abs {err.max():.2e} mean {err.mean():.2e}")
+        assert err.max() <= ATTN_ABS
 
 
 @pytest.mark.parametrize("wl,seed,case", [
-    ("c1", 3, dict()),                                    # one KV group: 8 XCDs share it
+    ("c1", 3, dict()),
     ("c1", 3, dict(N=1000)),                              # ragged tail
-    ("c1", 4, dict(B=2, Hq=8, Hkv=2, N=3072)),            # four groups, two XCDs each
-    ("c1", 4, dict(B=2, Hq=16, Hkv=4, N=1024)),           # eight groups, one XCD each
-    ("c1", 5, dict(B=4, Hq=8, Hkv=4, N=640)),             # sixteen groups, two per XCD
-    ("c1", 5, dict(B=3, Hq=4, Hkv=1, N=384)),             # three groups: the static grid
-    ("c1", 7, dict(B=2, Hq=4, Hkv=1, N=2560)),            # two groups, four XCDs each
-    ("c1", 7, dict(B=3, Hq=16, Hkv=8, N=256)),            # 24 groups, three per XCD
+    ("c1", 4, dict(B=2, Hq=8, Hkv=2, N=3072)),
+    ("c1", 4, dict(B=2, Hq=16, Hkv=4, N=1024)),
+    ("c1", 5, dict(B=4, Hq=8, Hkv=4, N=640)),
+    ("c1", 5, dict(B=3, Hq=4, Hkv=1, N=384)),
+    ("c1", 7, dict(B=2, Hq=4, Hkv=1, N=2560)),
+    ("c1", 7, dict(B=3, Hq=16, Hkv=8, N=256)),
     ("c1", 6, dict(Ls=256, Lb=128, N=1280, base_budget=512)),   # two sub-blocks per block
     ("c1", 6, dict(N=65)),
-    ("c2", 2, dict(N=16384)),
+    ("c2", 2, dict(N=16384)),                             # these two queue as they are
     ("c4", 1, dict(N=8192)),                              # four KV groups, G = 7
 ], ids=lambda x: x if isinstance(x, str) else None)
 def test_persistent_schedule_equals_static(wl, seed, case):
-    """With a scheduling workspace the sparse kernel runs persistent
-    workgroups over per-XCD queues with stealing; the output is bitwise the
-    static grid's (no workspace), also on a second call into the same
-    workspace (the counters are reset by each call)."""
+    """With a scheduling workspace and more items than two workgroups per CU
+    take at once, the sparse kernel runs persistent workgroups over per-XCD
+    queues with stealing; the output is bitwise the static grid's (no
+    workspace), also on a second call into the same workspace (the counters
+    are reset by each call).  The small cases give a workspace to launches
+    that do not queue; each is also run with its batch repeated until it
+    does."""
     w = synth.make(wl, seed, **case)
     say(f"[persistent] {wl} seed={seed} {case}")
     q, k, v = to_dev(w.q), to_dev(w.k), to_dev(w.v)
@@ -502,6 +596,8 @@ def test_persistent_schedule_equals_static(wl, seed, case):
                                out=o, workspace=ws)
         torch.cuda.synchronize()
         assert torch.equal(o, o_static), f"call {call}"
+    if n_items(w) <= queue_items():
+        large_launches(w, q, k, v, sel["idx"], sel["cnt"])
 
 
 @pytest.mark.parametrize("wl,seed,case", [
@@ -510,11 +606,16 @@ def test_persistent_schedule_equals_static(wl, seed, case):
     ("c1", 4, dict(Hq=8, Hkv=1, N=9000)),                    # one group, 568 items
     ("c1", 7, dict(B=2, Hq=16, Hkv=4, N=4096 - 90, Ls=256, Lb=128)),   # 1024 items
     ("c1", 7, dict(B=2, Hq=16, Hkv=4, N=2304, base_budget=1024)),   # longer items
+    ("c1", 7, dict(B=2, Hq=8, Hkv=1, N=4224 - 60)),          # two groups, four XCDs each
+    ("c1", 7, dict(B=3, Hq=16, Hkv=8, N=1408 - 30)),         # 24 groups, three per XCD
+    ("c1", 5, dict(B=3, Hq=4, Hkv=1, N=5632 - 17)),          # three groups: the static grid
 ], ids=lambda x: x if isinstance(x, str) else None)
 def test_persistent_queues(wl, seed, case):
     """The persistent schedule proper (more items than it has workgroups),
     with items short enough to draw the next ticket while they run and with
-    longer ones: bitwise the static grid's output, twice."""
+    longer ones: bitwise the static grid's output, twice.  (Three groups do
+    not divide the XCDs and keep the static grid.)"""
+    assert n_items(synth.make(wl, seed, **case, generate_tensors=False)) > queue_items()
     test_persistent_schedule_equals_static(wl, seed, case)
 
 
@@ -535,7 +636,8 @@ def test_binding_refuses_mismatched_tensors():
 
 
 def test_malformed_block_list_is_safe():
-    """Out-of-range, descending and oversized counts stop the list walk."""
+    """Out-of-range, descending and oversized counts stop the list walk, in
+    every kernel."""
     w = synth.make("c1", 4, N=512)
     q, k, v = to_dev(w.q), to_dev(w.k), to_dev(w.v)
     km = w.kmax
@@ -551,18 +653,19 @@ def test_malformed_block_list_is_safe():
         cnt[0, 2, s] = 10 ** 6                                    # count beyond kmax
         idx[0, 3, s, :3] = torch.tensor(own + [0])               # not ascending
         cnt[0, 3, s] = 3
-    o = eb.sparse_prefill_attn(q, k, v, idx.cuda(), cnt.cuda(), w.Ls, w.Lb, w.softmax_scale)
-    torch.cuda.synchronize()
-    of = o.float().cpu()
-    assert torch.isfinite(of).all()
-    assert (of[0, 1] == 0).all()                                  # nothing visible -> zeros
     rows = np.array([[0, h, i] for h in (0, 2, 3) for i in range(w.N)], np.int32)
     ref_idx = idx.numpy().copy()
     ref_cnt = np.full((1, w.Hq, w.CS), 2, np.int32)
     ref = oracle.attention(w.q, w.k, w.v, rows, w.softmax_scale, True, ref_idx, ref_cnt, w.Ls,
                            w.Lb)
-    got = of.numpy().astype(np.float64)[rows[:, 0], rows[:, 1], rows[:, 2]]
-    assert np.abs(got - ref).max() <= ATTN_ABS
+    idx, cnt = idx.cuda(), cnt.cuda()
+    small = eb.sparse_prefill_attn(q, k, v, idx, cnt, w.Ls, w.Lb, w.softmax_scale)
+    for o in (small, large_launches(w, q, k, v, idx, cnt)):
+        of = o.float().cpu()
+        assert torch.isfinite(of).all()
+        assert (of[0, 1] == 0).all()                              # nothing visible -> zeros
+        got = of.numpy().astype(np.float64)[rows[:, 0], rows[:, 1], rows[:, 2]]
+        assert np.abs(got - ref).max() <= ATTN_ABS
 
 
 def _crafted_scores(CS, CB, Hq, seed=5):
