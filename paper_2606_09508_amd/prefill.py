@@ -93,11 +93,11 @@ def _tables_fit(N, D, theta) -> bool:
 def rope_tables(N: int, D: int, theta: float, device):
     """cos / sin [N, D/2] (fp32) of the rotary embedding, half-split layout."""
     # (device may be anything a factory function takes)
-    if _tables_fit(N, D, theta) and not _observed() \
-            and _kernel_device(torch.empty(0, device=device).device):
+    dev = device if type(device) is torch.device else torch.empty(0, device=device).device
+    if _kernel_device(dev) and _tables_fit(N, D, theta) and not _observed():
         cos, sin = (torch.empty((N, (D + 1) // 2), dtype=torch.float32, device=device)
                     for _ in range(2))
-        if _plain(cos, sin):
+        if _ordinary(cos, sin):
             eb.rope_tables(cos, sin, D, theta)
             return cos, sin
     inv = 1.0 / (theta ** (torch.arange(0, D, 2, device=device, dtype=torch.float32) / D))
@@ -152,7 +152,7 @@ def _observed() -> bool:
     dispatch and function modes (a default device apart, which only concerns
     factory functions), functorch and forward-mode transforms."""
     C = torch._C
-    return (torch.compiler.is_compiling() or C._get_tracing_state() is not None
+    return (torch.compiler.is_compiling() or C._is_tracing()
             or C._len_torch_dispatch_stack() > 0
             or (C._len_torch_function_stack() > 0
                 and any(type(m) is not DeviceContext
@@ -161,22 +161,36 @@ def _observed() -> bool:
             or torch.autograd.forward_ad._current_level >= 0)
 
 
+def _quiet(dev) -> bool:
+    """Whether kernel calls on that device pass unnoticed: it is a GPU, nothing
+    looks on, and there is no autocast to another type than bf16 (under which
+    the products between the kernels are of that type)."""
+    return (_kernel_device(dev) and not _observed()
+            and not (torch.is_autocast_enabled(dev.type)
+                     and torch.get_autocast_dtype(dev.type) != torch.bfloat16))
+
+
+def _ordinary(*ts) -> bool:
+    """Ordinary tensors of one device with no gradient to record."""
+    dev, grad = ts[0].device, torch.is_grad_enabled()
+    for t in ts:
+        if type(t) not in (torch.Tensor, torch.nn.Parameter) or t.device != dev \
+                or (grad and t.requires_grad):
+            return False
+    return True
+
+
 def _plain(*ts) -> bool:
     """Whether a kernel call on these tensors computes all that the tensor
-    operations would: ordinary tensors of one GPU, no gradient to record,
-    nothing that looks on and no autocast to another type than bf16 (under
-    which the products between the kernels are of that type)."""
-    dev = ts[0].device
-    return (_kernel_device(dev)
-            and all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.device == dev for t in ts)
-            and not _observed()
-            and not (torch.is_autocast_enabled(dev.type)
-                     and torch.get_autocast_dtype(dev.type) != torch.bfloat16)
-            and not (torch.is_grad_enabled() and any(t.requires_grad for t in ts)))
+    operations would."""
+    return _quiet(ts[0].device) and _ordinary(*ts)
 
 
 def _dense16(*ts) -> bool:
-    return all(t.is_contiguous() and t.data_ptr() % 16 == 0 for t in ts)
+    for t in ts:
+        if not t.is_contiguous() or t.data_ptr() % 16:
+            return False
+    return True
 
 
 def _norm_fits(x, gain) -> bool:
@@ -190,20 +204,21 @@ def _adds(x, y) -> bool:
     """Whether ei_add_rmsnorm forms the residual sum x + y as the tensor sum
     would: y may carry gradients where x has none (an MLP or output projection
     being trained in an otherwise frozen layer), and may broadcast."""
-    return _plain(x, y) and y.dtype == x.dtype and y.shape == x.shape and _dense16(y)
+    return _ordinary(x, y) and y.dtype == x.dtype and y.shape == x.shape and _dense16(y)
 
 
-def _one_pass(x, w, shape: DecoderShape, cos, sin) -> bool:
+def _one_pass(x, w, shape: DecoderShape, cos, sin, quiet: bool | None = None) -> bool:
     """Whether the layer's norms, rotary embedding and SwiGLU run in this
     library's one-pass kernels; what those do not take goes through the tensor
     operations, which accept any of it."""
-    return (_plain(x, cos, sin, *w.values()) and shape.head_dim == 128
+    return ((_quiet(x.device) if quiet is None else quiet)
+            and _ordinary(x, cos, sin, *w.values()) and shape.head_dim == 128
             and shape.n_q_heads % shape.n_kv_heads == 0
             and w["w_gate"].shape == w["w_up"].shape and w["w_gate"].shape[-1] % 8 == 0
             and all(t.dtype == torch.bfloat16 for t in w.values())
-            and _norm_fits(x, w["norm1"]) and _norm_fits(x, w["norm2"])
-            and all(t.dtype == torch.float32 and tuple(t.shape) == (x.shape[1], 64)
-                    for t in (cos, sin)) and _dense16(cos, sin))
+            and _norm_fits(x, w["norm1"]) and w["norm2"].shape == w["norm1"].shape
+            and cos.dtype == sin.dtype == torch.float32
+            and cos.shape == sin.shape == (x.shape[1], 64) and _dense16(w["norm2"], cos, sin))
 
 
 def _layer(x, y, w, shape: DecoderShape, attn: Attention, cos, sin, trace=None):
@@ -212,9 +227,10 @@ def _layer(x, y, w, shape: DecoderShape, attn: Attention, cos, sin, trace=None):
     takes their sum in the pass that reads it."""
     B, N, _ = x.shape
     Hq, Hkv, D = shape.n_q_heads, shape.n_kv_heads, shape.head_dim
-    if y is not None and not _adds(x, y):
+    quiet = _quiet(x.device)   # once a layer: each look costs a small prompt ~2 us
+    if y is not None and not (quiet and _adds(x, y)):
         x, y = x + y, None
-    one_pass = _one_pass(x, w, shape, cos, sin)
+    one_pass = _one_pass(x, w, shape, cos, sin, quiet)
     if one_pass:
         x, h = eb.add_rmsnorm(x, y, w["norm1"], shape.rms_eps)
     else:
