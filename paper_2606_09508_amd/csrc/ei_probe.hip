@@ -425,7 +425,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
 // sharing each staged key tile.  Two row tiles per wave share it over twice
 // the rows but need ~190 VGPRs (2 waves per SIMD against 4): 5% slower on the
 // 128k layer.  Launches that would leave CUs idle take one-wave workgroups
-// (kSmallWaves; the rule is at launch_probe).
+// (kSmallWaves; the rule is at launch_pool_scores).
 constexpr int KT = 1;
 constexpr int kWaves = 4, kSmallWaves = 1;
 constexpr int kUnits = kWaves * 4 * KT;
@@ -977,15 +977,15 @@ hipError_t launch_fused_select(const ProbeShape& s, const Layout& lay, unsigned 
 //
 // A launch of at most kSmallGrid 16-unit workgroups (half the chip's 256 CUs;
 // three eighths if its rows are longer than kSmallRow blocks, which gain more
-// from key tiles shared by four waves) leaves most of the chip idle while each of its waves pools four segments in
-// turn: the query segments are then pooled by pool_kernel, a wave each, and
-// the scores kernel takes one-wave workgroups of 4 units.  Probe alone, 16-unit
-// against one-wave workgroups: 2 workgroups (4 heads, 1024 tokens) 22.3 / 16.4
-// us, 32 (32 heads, 2047 tokens) 46.1 / 19.0, 64 (3999) 33.4 / 20.2, 128 (8192)
-// 36.8 / 33.3, 64 (4 heads, 32768) 59.4 / 51.3; but 128 (4 heads, 65536) 96.6 /
-// 97.6, 224 (28 heads, 16384) 48.3 / 54.0 and 256 (32 heads, 16384) 55.0 /
-// 59.6: from there the separate pass over Q and the unshared key tiles cost
-// more.
+// from key tiles shared by four waves) leaves most of the chip idle while each
+// of its waves pools four segments in turn: the query segments are then pooled
+// by pool_kernel, a wave each, and the scores kernel takes one-wave workgroups
+// of 4 units.  Probe alone, 16-unit against one-wave workgroups: 2 workgroups
+// (4 heads, 1024 tokens) 22.3 / 16.4 us, 32 (32 heads, 2047 tokens) 46.1 /
+// 19.0, 64 (3999) 33.4 / 20.2, 128 (8192) 36.8 / 33.3, 64 (4 heads, 32768) 59.4
+// / 51.3; but 128 (4 heads, 65536) 96.6 / 97.6, 224 (28 heads, 16384) 48.3 /
+// 54.0 and 256 (32 heads, 16384) 55.0 / 59.6: from there the separate pass over
+// Q and the unshared key tiles cost more.
 constexpr int64_t kSmallGrid = 128, kSmallGridLong = 96;
 constexpr int kSmallRow = 256;
 template <int MODE>
