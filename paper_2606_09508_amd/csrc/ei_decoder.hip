@@ -32,6 +32,10 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kNormMaxCols = 16384;
+// A launch's threads are counted in 32 bits and one of more does less without
+// an error, so work of more workgroups than these takes several launches.
+constexpr int64_t kMaxGrid = (1ll << 31) / kThreads;
+unsigned launch_grid(int64_t left) { return (unsigned)(left < kMaxGrid ? left : kMaxGrid); }
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -130,9 +134,10 @@ constexpr int kRopeHeads = 8, kRopePos = kThreads / 8;
 __global__ __launch_bounds__(kThreads) void rope_heads_kernel(
     const uint16_t* __restrict__ qi, const uint16_t* __restrict__ ki,
     const uint16_t* __restrict__ vi, const float* __restrict__ cosv,
-    const float* __restrict__ sinv, int N, int Hq, int Hkv, int n_pos,
+    const float* __restrict__ sinv, int N, int Hq, int Hkv, int n_pos, unsigned g0,
     uint16_t* __restrict__ qo, uint16_t* __restrict__ ko, uint16_t* __restrict__ vo) {
-  const int pb = (int)(blockIdx.x % (unsigned)n_pos), hb = (int)(blockIdx.x / (unsigned)n_pos);
+  const unsigned wg = g0 + blockIdx.x;   // (g0: the launch's first)
+  const int pb = (int)(wg % (unsigned)n_pos), hb = (int)(wg / (unsigned)n_pos);
   const int groups = (Hq + 2 * Hkv + kRopeHeads - 1) / kRopeHeads;
   const int b = hb / groups, h0 = (hb % groups) * kRopeHeads;
   const int c = threadIdx.x & 7;
@@ -190,10 +195,12 @@ __global__ __launch_bounds__(kThreads) void rope_heads_kernel(
 // cos / sin of position * theta^(-2i / D), [N][half], the fp32 operations of
 // the tensor form one after another (power, reciprocal, product, cos, sin) in
 // one launch: as ten, the tables of a short prompt took 45 us of it.
-__global__ __launch_bounds__(kThreads) void rope_tables_kernel(int64_t n, int half, float D,
-                                                              float theta, float* __restrict__ cosv,
+// (e0: the launch's first element)
+__global__ __launch_bounds__(kThreads) void rope_tables_kernel(int64_t e0, int64_t n, int half,
+                                                              float D, float theta,
+                                                              float* __restrict__ cosv,
                                                               float* __restrict__ sinv) {
-  const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int64_t e = e0 + (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (e >= n) return;
   const int64_t pos = e / half;
   const int i = (int)(e - pos * half);
@@ -242,13 +249,19 @@ __global__ __launch_bounds__(kThreads) void swiglu_kernel(const uint16_t* g, con
 template <int T, int CH>
 void launch_norm_t(const uint16_t* x, const uint16_t* y, const uint16_t* gain, int64_t rows,
                    int cols, float eps, uint16_t* sum_out, uint16_t* out, hipStream_t stream) {
-  const int64_t per = kThreads / T, grid = (rows + per - 1) / per;
-  if (y)
-    hipLaunchKernelGGL((add_rmsnorm_kernel<T, CH, true>), dim3((unsigned)grid), dim3(kThreads), 0,
-                       stream, x, y, gain, rows, cols, eps, sum_out, out);
-  else
-    hipLaunchKernelGGL((add_rmsnorm_kernel<T, CH, false>), dim3((unsigned)grid), dim3(kThreads), 0,
-                       stream, x, y, gain, rows, cols, eps, sum_out, out);
+  constexpr int64_t per = kThreads / T;
+  const int64_t groups = (rows + per - 1) / per;
+  for (int64_t g0 = 0; g0 < groups; g0 += kMaxGrid) {
+    const dim3 grid(launch_grid(groups - g0));
+    const int64_t left = rows - g0 * per;
+    const size_t at = (size_t)(g0 * per) * cols;
+    if (y)
+      hipLaunchKernelGGL((add_rmsnorm_kernel<T, CH, true>), grid, dim3(kThreads), 0, stream, x + at,
+                         y + at, gain, left, cols, eps, sum_out + at, out + at);
+    else
+      hipLaunchKernelGGL((add_rmsnorm_kernel<T, CH, false>), grid, dim3(kThreads), 0, stream,
+                         x + at, nullptr, gain, left, cols, eps, nullptr, out + at);
+  }
 }
 
 hipError_t launch_add_rmsnorm(const uint16_t* x, const uint16_t* y, const uint16_t* gain,
@@ -268,17 +281,22 @@ hipError_t launch_rope_heads(const uint16_t* q, const uint16_t* k, const uint16_
                              uint16_t* qo, uint16_t* ko, uint16_t* vo, hipStream_t stream) {
   const int n_pos = (N + kRopePos - 1) / kRopePos;
   const int groups = (Hq + 2 * Hkv + kRopeHeads - 1) / kRopeHeads;
-  hipLaunchKernelGGL(rope_heads_kernel, dim3((unsigned)((int64_t)B * groups * n_pos)),
-                     dim3(kThreads), 0, stream, q, k, v, cosv, sinv, N, Hq, Hkv, n_pos, qo, ko,
-                     vo);
+  const int64_t total = (int64_t)B * groups * n_pos;
+  for (int64_t g0 = 0; g0 < total; g0 += kMaxGrid)
+    hipLaunchKernelGGL(rope_heads_kernel, dim3(launch_grid(total - g0)), dim3(kThreads), 0, stream,
+                       q, k, v, cosv, sinv, N, Hq, Hkv, n_pos, (unsigned)g0, qo, ko, vo);
   return hipGetLastError();
 }
 
 hipError_t launch_swiglu(const uint16_t* g, const uint16_t* u, int64_t n, uint16_t* out,
                          hipStream_t stream) {
-  const int64_t chunks = n / 8, per = kThreads * kSwigluChunks;
-  hipLaunchKernelGGL(swiglu_kernel, dim3((unsigned)((chunks + per - 1) / per)), dim3(kThreads), 0,
-                     stream, g, u, chunks, out);
+  constexpr int64_t per = kThreads * kSwigluChunks;
+  const int64_t chunks = n / 8, groups = (chunks + per - 1) / per;
+  for (int64_t g0 = 0; g0 < groups; g0 += kMaxGrid) {
+    const size_t at = (size_t)(g0 * per * 8);
+    hipLaunchKernelGGL(swiglu_kernel, dim3(launch_grid(groups - g0)), dim3(kThreads), 0, stream,
+                       g + at, u + at, chunks - g0 * per, out + at);
+  }
   return hipGetLastError();
 }
 
@@ -330,13 +348,15 @@ ei_status ei_rope_tables(int32_t seq_len, int32_t head_dim, float theta, float* 
                          float* sin_table, void* stream) {
   if (seq_len < 0 || head_dim <= 0 || !(theta > 0.0f)) return EI_ERR_SHAPE;
   const int32_t half = (int32_t)(((int64_t)head_dim + 1) / 2);
-  const int64_t n = (int64_t)seq_len * half, grid = (n + ei::kThreads - 1) / ei::kThreads;
-  if (grid > INT_MAX) return EI_ERR_SHAPE;
+  const int64_t n = (int64_t)seq_len * half, groups = (n + ei::kThreads - 1) / ei::kThreads;
+  if (groups > INT_MAX) return EI_ERR_SHAPE;
   if (n == 0) return EI_OK;
   if (!cos_table || !sin_table) return EI_ERR_NULL;
   if (((uintptr_t)cos_table | (uintptr_t)sin_table) & 3) return EI_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(ei::rope_tables_kernel, dim3((unsigned)grid), dim3(ei::kThreads), 0,
-                     (hipStream_t)stream, n, half, (float)head_dim, theta, cos_table, sin_table);
+  for (int64_t g0 = 0; g0 < groups; g0 += ei::kMaxGrid)
+    hipLaunchKernelGGL(ei::rope_tables_kernel, dim3(ei::launch_grid(groups - g0)),
+                       dim3(ei::kThreads), 0, (hipStream_t)stream, g0 * ei::kThreads, n, half,
+                       (float)head_dim, theta, cos_table, sin_table);
   return ei::from_hip(hipGetLastError());
 }
 

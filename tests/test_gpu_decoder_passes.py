@@ -63,6 +63,48 @@ def test_rope_tables(N, D, theta):
     assert torch.equal(cos, torch.cos(ang)) and torch.equal(sin, torch.sin(ang))
 
 
+def _edges(n, step):
+    """Slices at both ends of n rows and around every multiple of step."""
+    return [slice(max(at - 500, 0), min(at + 500, n)) for at in [*range(0, n, step), n]]
+
+
+def test_add_rmsnorm_of_more_rows_than_a_launch_takes():
+    """A launch takes fewer than 2^32 threads, here 2^26 rows."""
+    rows, cols = 2 ** 26 + 5, 8
+    x, y = (_rand((4099, cols), 5 + i).cuda().repeat(rows // 4099 + 1, 1)[:rows] for i in range(2))
+    g = _rand((cols,), 3).cuda()
+    s, h = eb.add_rmsnorm(x, y, g, 1e-5)
+    for part in _edges(rows, 2 ** 25):
+        ref = eb.add_rmsnorm(x[part], y[part], g, 1e-5)
+        assert torch.equal(s[part], ref[0]) and torch.equal(h[part], ref[1]), part
+
+
+def test_rope_heads_of_more_sequences_than_a_launch_takes():
+    B = 2 ** 24 + 3
+    q, k, v = (_rand((4099, 1, 1, 128), 4 + i).cuda().repeat(B // 4099 + 1, 1, 1, 1)[:B]
+               for i in range(3))
+    cos, sin = pf.rope_tables(2, 128, 1e4, torch.device("cuda:0"))
+    cos, sin = cos[1:], sin[1:]
+    got = eb.rope_heads(q, k, v, cos, sin)
+    for part in _edges(B, 2 ** 23):
+        for a, b in zip(got, eb.rope_heads(q[part], k[part], v[part], cos, sin)):
+            assert torch.equal(a[part], b), part
+    del q, k, v, got
+    torch.cuda.empty_cache()   # (26 GB)
+
+
+def test_rope_tables_of_more_values_than_a_launch_takes():
+    N, D, dev = 2 ** 26 + 3, 128, torch.device("cuda:0")
+    cos, sin = pf.rope_tables(N, D, 1e4, dev)
+    inv = 1.0 / (1e4 ** (torch.arange(0, D, 2, device=dev, dtype=torch.float32) / D))
+    pos = torch.arange(N, device=dev, dtype=torch.float32)
+    for part in _edges(N, 2 ** 25):
+        ang = pos[part][:, None] * inv
+        assert torch.equal(cos[part], torch.cos(ang)) and torch.equal(sin[part], torch.sin(ang)), part
+    del cos, sin
+    torch.cuda.empty_cache()   # (34 GB)
+
+
 @pytest.mark.parametrize("B,N,Hq,Hkv", [(1, 1, 1, 1), (1, 33, 4, 2), (2, 31, 7, 1), (1, 64, 32, 8),
                                         (3, 100, 5, 5)])
 def test_rope_heads(B, N, Hq, Hkv):
