@@ -62,7 +62,8 @@ typedef enum {
   EI_ERR_UNSUPPORTED = -3, /* valid but not implemented here (e.g. D != 128,
                               a misaligned pointer) */
   EI_ERR_WORKSPACE = -4,   /* workspace missing or smaller than required */
-  EI_ERR_LAUNCH = -5       /* a kernel launch failed (hipGetLastError) */
+  EI_ERR_LAUNCH = -5       /* a kernel launch failed (hipGetLastError), or would have
+                              2^32 threads or more */
 } ei_status;
 
 /* Problem sizes: batch B, query heads Hq, key/value heads Hkv, sequence N,

@@ -886,6 +886,7 @@ hipError_t launch_t(const uint16_t* q, const uint16_t* k, const uint16_t* v, con
   } else {
     sched = nullptr;
   }
+  if (!launch_fits(grid, kThreads)) return hipErrorInvalidConfiguration;
   const float sc_log2 = (float)((double)s.softmax_scale * 1.4426950408889634);
   hipLaunchKernelGGL((attn_kernel<MODE, SUB>), dim3((unsigned)grid), dim3(kThreads), 0, stream,
                      q, k, v, o, s.B, s.Hq, s.Hkv, s.N, n_tiles, s.Ls, s.CS, s.CB, sc_log2, bidx,
@@ -1050,6 +1051,7 @@ hipError_t launch_union_t(const uint16_t* q, const uint16_t* k, const uint16_t* 
   const int n_tiles = (s.N + kTileQ - 1) / kTileQ;
   const int npair = (s.Hq / s.Hkv + 1) / 2;
   const int64_t grid = (int64_t)s.B * s.Hkv * npair * n_tiles;
+  if (!launch_fits(grid, kUnionThreads)) return hipErrorInvalidConfiguration;
   const float sc_log2 = (float)((double)s.softmax_scale * 1.4426950408889634);
   hipLaunchKernelGGL((attn_union_kernel<SUB>), dim3((unsigned)grid), dim3(kUnionThreads), 0,
                      stream, q, k, v, o, s.B, s.Hq, s.Hkv, s.N, n_tiles, s.Ls, s.CS, s.CB,

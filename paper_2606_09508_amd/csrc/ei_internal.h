@@ -108,6 +108,12 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x) {
 // Host launchers (arguments already validated; B, N > 0)
 // ----------------------------------------------------------------------------
 
+// A launch's threads are counted in 32 bits, and one of more does less without
+// an error: such calls (millions of sequences of a few tokens) are refused.
+inline bool launch_fits(int64_t workgroups, int threads) {
+  return workgroups < (1ll << 32) / threads;
+}
+
 struct ProbeShape {
   int B, Hq, Hkv, N, Ls, Lb, CS, CB, r;
 };

@@ -948,6 +948,7 @@ hipError_t launch_pool(const uint16_t* q, const uint16_t* k, const ProbeShape& s
   const int64_t nq = (int64_t)s.B * s.Hq * s.CS;
   const int64_t items = (int64_t)s.B * s.Hkv * CBt * kTileBlocks + (pool_q ? nq : 0);
   const int64_t grid = (items + kPoolWaves - 1) / kPoolWaves;
+  if (!launch_fits(grid, kPoolThreads)) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL(pool_kernel, dim3((unsigned)grid), dim3(kPoolThreads), 0, stream, q, k, s.B,
                      s.Hq, s.Hkv, s.N, s.Ls, s.Lb, s.CS, s.CB, CBt, sgn, ws, lay, pool_q ? 0 : nq,
                      sched);
@@ -999,8 +1000,9 @@ hipError_t launch_pool_scores(const uint16_t* q, const uint16_t* k, const ProbeS
   // skip the residual MFMA where it moves no logit by 2^-30 or more
   const float tau = probe_scale == 0.0 ? INFINITY : (float)(0x1p-30 / ps_abs);
   const int64_t n_groups = (int64_t)s.B * s.Hkv, U = (int64_t)(s.Hq / s.Hkv) * s.CS;
-  const bool small = n_groups * ((U + kUnits - 1) / kUnits) <=
-                     (s.CB <= kSmallRow ? kSmallGrid : kSmallGridLong);
+  const int64_t wgs = n_groups * ((U + kUnits - 1) / kUnits);
+  const bool small = wgs <= (s.CB <= kSmallRow ? kSmallGrid : kSmallGridLong);
+  if (!launch_fits(wgs, kWaves * kWave)) return hipErrorInvalidConfiguration;
   hipError_t e = launch_pool(q, k, s, sgn, ws, lay, CBt, sched, small, stream);
   if (e != hipSuccess) return e;
   auto launch = [&](auto kern, int waves) {

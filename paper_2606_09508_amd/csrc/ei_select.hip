@@ -284,6 +284,7 @@ hipError_t launch_topk_t(const float* log_scores, const int32_t* kb, const Selec
                          int32_t* idx, int32_t* cnt, hipStream_t stream) {
   const int64_t rows = (int64_t)s.B * s.Hq * s.CS;
   const int64_t grid = (rows + (kThreads / kWave) - 1) / (kThreads / kWave);
+  if (!launch_fits(grid, kThreads)) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL(topk_kernel<SLOTS>, dim3((unsigned)grid), dim3(kThreads), 0, stream,
                      log_scores, kb, rows, s.CS, s.CB, s.r, s.kmax, idx, cnt);
   return hipGetLastError();
@@ -297,6 +298,7 @@ bool select_supported(const SelectShape& s) { return s.CB <= 128 * kWave; }
 
 hipError_t launch_budget(const float* entropy, const SelectShape& s, uint8_t* rigid,
                          int32_t* budget_blocks, hipStream_t stream) {
+  if (!launch_fits((int64_t)s.B * s.Hq, kThreads)) return hipErrorInvalidConfiguration;
   if (s.mode == EI_CLASSIFY_GQA_GROUP)
     hipLaunchKernelGGL(budget_kernel<true>, dim3((unsigned)(s.B * s.Hq)), dim3(kThreads), 0,
                        stream, entropy, s.Hq, s.CS, s.r, s.Lb, s.e_t, s.alpha, s.delta_t, s.Bh,
@@ -316,7 +318,9 @@ hipError_t launch_select(const float* log_scores, const float* entropy, const Se
     const BudgetArgs p{entropy, s.Hq, s.G, s.Lb, s.Bh, s.mult, s.mode, s.e_t, s.alpha, s.delta_t,
                        rigid, budget_blocks};
     const int64_t rows = (int64_t)s.B * s.Hq * s.CS;
-    const dim3 grid((unsigned)((rows + kWavesPerGroup - 1) / kWavesPerGroup));
+    const int64_t wgs = (rows + kWavesPerGroup - 1) / kWavesPerGroup;
+    if (!launch_fits(wgs, kThreads)) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)wgs);
     if (s.mode == EI_CLASSIFY_GQA_GROUP)
       hipLaunchKernelGGL(select_short_kernel<true>, grid, dim3(kThreads), 0, stream, log_scores, p,
                          rows, s.CS, s.CB, s.r, s.kmax, block_idx, block_cnt);

@@ -635,6 +635,33 @@ def test_binding_refuses_mismatched_tensors():
     torch.cuda.synchronize()
 
 
+def test_more_threads_than_a_launch_takes_are_refused():
+    """A launch counts its threads in 32 bits: past 2^24 workgroups (one-token
+    sequences here) the calls fail instead of leaving outputs unwritten."""
+    B = 2 ** 24
+    x = torch.ones((B, 1, 1, 128), dtype=torch.bfloat16, device="cuda")
+    o = torch.empty_like(x)
+    idx = torch.zeros((B, 1, 1, 1), dtype=torch.int32, device="cuda")
+    cnt = torch.ones((B, 1, 1), dtype=torch.int32, device="cuda")
+
+    def dense(n):
+        eb.dense_prefill_attn(x[:n], x[:n], x[:n], 1.0, True, out=o[:n])
+
+    def sparse(n, **kw):
+        eb.sparse_prefill_attn(x[:n], x[:n], x[:n], idx[:n], cnt[:n], 128, 64, 1.0, out=o[:n], **kw)
+    for call, n in ((dense, B), (lambda n: sparse(n, persistent=False), B),
+                    (lambda n: sparse(n, gqa_union=True), B // 2)):   # (512 threads a workgroup)
+        with pytest.raises(eb.EIError):
+            call(n)
+        o.zero_()
+        call(n - 8)   # the most a launch takes
+        assert bool((o[:n - 8] == 1.0).all()) and not bool(o[n - 8:].any())
+    sparse(B)   # (a queue's grid does not grow with its items)
+    assert bool((o == 1.0).all())
+    with pytest.raises(eb.EIError):   # (16 key block slots of a wave each per KV head)
+        eb.entropy_probe(x[:B // 4], x[:B // 4], 128, 64)
+
+
 def test_malformed_block_list_is_safe():
     """Out-of-range, descending and oversized counts stop the list walk, in
     every kernel."""
