@@ -200,6 +200,23 @@ def test_probe_workgroup_sizes(wl, case):
     say(f"[probe {wl} {case}] entropy rel {hrel:.2e} L {lerr:.2e}")
 
 
+@pytest.mark.parametrize("N", [1, 4, 15, 16, 17, 48, 61, 63, 64, 79, 81, 451])
+@pytest.mark.parametrize("Ls", [128, 512])
+def test_probe_last_rows(N, Ls):
+    """Every count of rows left over in a last segment or block past whole
+    batches of 64 rows and past 16, pooled by either kernel: the same bits, and
+    ln A and entropy against the oracle."""
+    w = synth.make("c1", 13, N=N, Ls=Ls)
+    q, k = to_dev(w.q), to_dev(w.k)
+    ls, en = eb.entropy_probe(q, k, w.Ls, w.Lb, w.probe_scale)
+    big = eb.entropy_probe(q.repeat(160, 1, 1, 1), k.repeat(160, 1, 1, 1), w.Ls, w.Lb, w.probe_scale)
+    torch.cuda.synchronize()
+    vis = (torch.arange(w.CB) < (torch.arange(w.CS)[:, None] + 1) * (Ls // w.Lb)).cuda()
+    assert torch.equal(big[1][159], en[0])
+    assert torch.equal(big[0][159].masked_fill(~vis, 0.0), ls[0].masked_fill(~vis, 0.0))
+    check_probe(w, {"ls": ls.cpu().numpy(), "en": en.cpu().numpy()})
+
+
 def _span_inputs(N=1024, Hq=4, Hkv=1, seed=11):
     """Query / key elements far below each pooled vector's maximum, so that
     the probe's fixed-point grid (2^-13 of the maximum's binade) leaves
