@@ -48,6 +48,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 // Both passes must form bitwise the same logits (the argmax's offset from the
@@ -396,31 +397,32 @@ __device__ __forceinline__ void pool_item(const uint16_t* __restrict__ src, int 
   }
 }
 
-// One wave per item: a query segment (B*Hq*C_S items, the first) or a key
-// block slot (B*Hkv*C_Bt*16 items); item_offset selects where the launch
-// starts (the scores kernel pools the query segments it uses itself).  sched:
-// queue counters of a later launch to zero, or null.
+// One wave per item: a query segment (B*Hq*C_S items, q_per to each of the
+// first q_wgs workgroups; none where the scores kernel pools the segments it
+// uses itself) or a key block slot (B*Hkv*C_Bt*16 items, kPoolWaves to a
+// workgroup, so that a tile's records are written from one XCD).  sched: queue
+// counters of a later launch to zero, or null.
 __global__ __launch_bounds__(kPoolThreads) void pool_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int B, int Hq, int Hkv,
     int N, int Ls, int Lb, int CS, int CB, int CBt, double sgn, unsigned char* __restrict__ ws,
-    Layout lay, int64_t item_offset, uint32_t* __restrict__ sched) {
+    Layout lay, unsigned q_wgs, unsigned q_per, uint32_t* __restrict__ sched) {
   if (sched != nullptr && blockIdx.x == 0 && threadIdx.x < kSchedCounters) sched[threadIdx.x] = 0u;
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t item = item_offset + (int64_t)blockIdx.x * kPoolWaves +
-                       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t nq = (int64_t)B * Hq * CS, nk = (int64_t)B * Hkv * CBt * kTileBlocks;
-  if (item >= nq + nk) return;
+  const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // 32-bit divisions: segments and key tiles number under 2^31 (64-bit ones,
   // here and in the scores kernel's prologue: probe 0-2% slower)
-  if (item < nq) {
-    const uint32_t head = (uint32_t)item / (uint32_t)CS;
-    pool_item<true>(q, N, Ls, CS, CB, CBt, sgn, ws, lay, head,
-                    (int)((uint32_t)item - head * (uint32_t)CS), lane);
+  if (blockIdx.x < q_wgs) {
+    const uint32_t item = blockIdx.x * q_per + wave, head = item / (uint32_t)CS;
+    if (wave >= q_per || item >= (uint32_t)(B * Hq) * (uint32_t)CS) return;
+    pool_item<true>(q, N, Ls, CS, CB, CBt, sgn, ws, lay, head, (int)(item - head * (uint32_t)CS),
+                    lane);
   } else {
-    const uint32_t tile = (uint32_t)((item - nq) / kTileBlocks), head = tile / (uint32_t)CBt;
+    const int64_t item = (int64_t)(blockIdx.x - q_wgs) * kPoolWaves + wave;
+    if (item >= (int64_t)B * Hkv * CBt * kTileBlocks) return;
+    const uint32_t tile = (uint32_t)(item / kTileBlocks), head = tile / (uint32_t)CBt;
     pool_item<false>(k, N, Lb, CS, CB, CBt, sgn, ws, lay, head,
                      (int)((tile - head * (uint32_t)CBt) * kTileBlocks) +
-                         (int)((item - nq) % kTileBlocks),
+                         (int)(item % kTileBlocks),
                      lane);
   }
 }
@@ -950,17 +952,26 @@ constexpr size_t kLdsBytes = 160 * 1024;
 constexpr size_t kFusedStaticLds = 2 * kStageBytes;   // stage buffers of the TPS = 1 instance
 
 // The key blocks, and with pool_q the query segments (else the scores kernel
-// pools them).
+// pools them), dealt out over the chip's kPoolCus CUs: eight segments read by
+// one CU wait for its load path (probe, 16-unit workgroups / eight segments to
+// a CU / one: 16 heads, 256 tokens, L_S 256 17.6 / 19.3 / 13.4 us; 8 heads, 393
+// tokens, L_S 512 22.7 / 26.1 / 15.6; 4 heads, 1000 tokens, L_S 256 50.5 / 18.1 /
+// 13.9).  The key blocks keep their order: a tile's slots dealt out too, its
+// records are written line by line from several XCDs (32 heads, 4096 tokens
+// 24.0 -> 27.3, whole tiles 22.3).
+constexpr int64_t kPoolCus = 256;
 hipError_t launch_pool(const uint16_t* q, const uint16_t* k, const ProbeShape& s, double sgn,
                        unsigned char* ws, const Layout& lay, int CBt, uint32_t* sched,
                        bool pool_q, hipStream_t stream) {
-  const int64_t nq = (int64_t)s.B * s.Hq * s.CS;
-  const int64_t items = (int64_t)s.B * s.Hkv * CBt * kTileBlocks + (pool_q ? nq : 0);
-  const int64_t grid = (items + kPoolWaves - 1) / kPoolWaves;
+  const int64_t nq = pool_q ? (int64_t)s.B * s.Hq * s.CS : 0;
+  const int64_t nk = (int64_t)s.B * s.Hkv * CBt * kTileBlocks;
+  const int64_t q_per = std::min<int64_t>((nq + kPoolCus - 1) / kPoolCus, kPoolWaves);
+  const int64_t q_wgs = nq ? (nq + q_per - 1) / q_per : 0;
+  const int64_t grid = q_wgs + (nk + kPoolWaves - 1) / kPoolWaves;
   if (!launch_fits(grid, kPoolThreads)) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL(pool_kernel, dim3((unsigned)grid), dim3(kPoolThreads), 0, stream, q, k, s.B,
-                     s.Hq, s.Hkv, s.N, s.Ls, s.Lb, s.CS, s.CB, CBt, sgn, ws, lay, pool_q ? 0 : nq,
-                     sched);
+                     s.Hq, s.Hkv, s.N, s.Ls, s.Lb, s.CS, s.CB, CBt, sgn, ws, lay, (unsigned)q_wgs,
+                     (unsigned)q_per, sched);
   return hipGetLastError();
 }
 

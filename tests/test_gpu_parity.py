@@ -188,6 +188,10 @@ def test_path_parity_small(case, seed):
     ("c4", dict(N=4096 + 33, n_spans=2)),         # 60, G = 7, residual tiles
     ("c2", dict(N=16384 + 192, Ls=256, Lb=128)),  # 136, longer segments and blocks
     ("c2", dict(N=16384 - 60, Ls=256, Lb=64)),    # 128
+    # pool_kernel: 256, 257 and 1400 query segments, 1, 2 and 6 to a workgroup
+    ("c1", dict(Hq=1, Hkv=1, N=256 * 128 - 5)),
+    ("c1", dict(Hq=1, Hkv=1, N=257 * 128)),
+    ("c1", dict(Hq=7, Hkv=1, N=200 * 128)),
 ], ids=lambda x: x if isinstance(x, str) else ",".join(f"{k}={v}" for k, v in x.items()))
 def test_probe_workgroup_sizes(wl, case):
     """Both workgroup sizes of the scores kernel at the edge of the rule that
