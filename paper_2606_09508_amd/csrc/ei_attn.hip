@@ -170,8 +170,11 @@ __device__ __forceinline__ void issue_stage(unsigned char* stage, const uint16_t
     copy_rows_to_lds<NC>(vb, vo, dst + kTileBytes);
     return;
   }
+  // The block that holds the sequence's end.  (Opaque: its row offsets are
+  // formed here, not kept across the loop.)
+  asm volatile("" : "+v"(lane));
 #pragma unroll
-  for (int j = 0; j < NC; ++j) {   // the block that holds the sequence's end
+  for (int j = 0; j < NC; ++j) {
     const int row = 4 * NC * wave + 4 * j + (lane >> 4), pos = lane & 15;
     const uint32_t roff = (uint32_t)((min(k0 + row, N - 1) - kc) * kRowBytes);
     copy_row_to_lds(kb, roff + 16 * swz(row, pos), dst + 1024 * j);
