@@ -15,7 +15,7 @@
 // Here each operand is read once and each result written once:
 //   add_rmsnorm, 8192 x 4096:                    43 us, 6.3 TB/s (23 us without the sum)
 //   rope_heads, 8192 tokens, 32 + 8 + 8 heads:   42 us, 4.8 TB/s
-//   swiglu, 8192 x 14336:                        127 us, 5.6 TB/s
+//   swiglu, 8192 x 14336:                        124 us, 5.7 TB/s
 // Every value is computed in fp32 with the roundings to bf16 where the tensor
 // operations have them (the sum, silu, the product, the rotated pair), so the
 // results differ from theirs only by the order of a row's sum of squares.
@@ -211,12 +211,13 @@ __global__ __launch_bounds__(kThreads) void rope_tables_kernel(int64_t e0, int64
   sinv[e] = sinf(ang);
 }
 
-// As the tensor operation has it, with its exponential and its division, so
-// that every value is the same.  (With a base-2 exponential of a rounded
-// product and an approximate reciprocal 18 of the 65536 bf16 values differed,
-// the large negative ones by their overflow; the same 127 us at 8192 x 14336,
-// 2-3 us less where the operands are in cache: 2047 x 14336 26.5 / 28.9.)
-__device__ __forceinline__ float silu(float x) { return x / (1.0f + expf(-x)); }
+// x / (1 + exp(-x)), every bf16 value of x rounding to the tensor operation's
+// result.  That takes the IEEE division (an approximate reciprocal misrounds
+// x = 5.9375); the exponential may be the base-2 instruction of a rounded
+// product (2047 x 14336, operands in cache: 26.5 us, with expf 29.1).
+__device__ __forceinline__ float silu(float x) {
+  return x / (1.0f + __builtin_amdgcn_exp2f(x * -1.4426950408889634f));
+}
 
 // Two chunks of 8 elements per thread.
 constexpr int kSwigluChunks = 2;
