@@ -954,9 +954,9 @@ constexpr size_t kFusedStaticLds = 2 * kStageBytes;   // stage buffers of the TP
 // The key blocks, and with pool_q the query segments (else the scores kernel
 // pools them), dealt out over the chip's kPoolCus CUs: eight segments read by
 // one CU wait for its load path (probe, 16-unit workgroups / eight segments to
-// a CU / one: 16 heads, 256 tokens, L_S 256 17.6 / 19.3 / 13.4 us; 8 heads, 393
-// tokens, L_S 512 22.7 / 26.1 / 15.6; 4 heads, 1000 tokens, L_S 256 50.5 / 18.1 /
-// 13.9).  The key blocks keep their order: a tile's slots dealt out too, its
+// a CU / one: 16 heads, 256 tokens, L_S 256 18.0 / 18.2 / 13.6 us; 2 x 8 heads,
+// 393 tokens, L_S 512 20.5 / 20.7 / 15.6; 4 heads, 1000 tokens, L_S 256 40.1 /
+// 16.5 / 14.3).  The key blocks keep their order: a tile's slots dealt out too, its
 // records are written line by line from several XCDs (32 heads, 4096 tokens
 // 24.0 -> 27.3, whole tiles 22.3).
 constexpr int64_t kPoolCus = 256;
@@ -1002,10 +1002,10 @@ hipError_t launch_fused_select(const ProbeShape& s, const Layout& lay, unsigned 
 // of its waves pools four segments in turn: the query segments are then pooled
 // by pool_kernel, a wave each, and the scores kernel takes one-wave workgroups
 // of 4 units.  Probe alone, 16-unit against one-wave workgroups: 2 workgroups
-// (4 heads, 1024 tokens) 22.3 / 16.4 us, 32 (32 heads, 2047 tokens) 46.1 /
-// 19.0, 64 (3999) 33.4 / 20.2, 128 (8192) 36.8 / 33.3, 64 (4 heads, 32768) 59.4
-// / 51.3; but 128 (4 heads, 65536) 96.6 / 97.6, 224 (28 heads, 16384) 48.3 /
-// 54.0 and 256 (32 heads, 16384) 55.0 / 59.6: from there the separate pass over
+// (4 heads, 1024 tokens) 21.8 / 12.9 us, 32 (32 heads, 2047 tokens) 35.4 /
+// 17.2, 64 (3999) 29.8 / 20.1, 128 (8192) 36.2 / 33.3, 64 (4 heads, 32768) 59.4
+// / 51.0; but 128 (4 heads, 65536) 94.2 / 96.2, 224 (28 heads, 16384) 47.8 /
+// 53.3 and 256 (32 heads, 16384) 54.6 / 59.3: from there the separate pass over
 // Q and the unshared key tiles cost more.
 constexpr int64_t kSmallGrid = 128, kSmallGridLong = 96;
 constexpr int kSmallRow = 256;
